@@ -242,6 +242,15 @@ pcr_status pcr_append_kv(const pcr_kv_pool *pool, const void *k_new, const void 
  * computed in the same launch by a decode workgroup (the key range split over its
  * waves, the same numerics as pcr_decode_attn), and such rows are spread over the
  * prefill row tiles of the launch so that they run beside them.
+ * Small launches: when a launch has too few workgroups for the device's compute units
+ * and long keys (a short suffix on a long prefix), the keys of each row tile are cut into
+ * chunks processed in parallel and merged by a second kernel on the same stream, with
+ * the same numerics. The partial results go to scratch the library holds per device
+ * (eight launches' worth, about 140 MB, until the process ends); a launch takes its
+ * part when it runs and gives it back, so calls on any streams and threads and replays
+ * of captured graphs may overlap, each with its own out as ever. The chunks follow
+ * from the lengths alone, so repeated calls give identical bits; a launch that finds
+ * eight others holding the scratch runs without chunks (same numerics, other roundings).
  */
 pcr_status pcr_prefix_prefill_attn(const void *q, const pcr_kv_pool *pool,
                                    const int32_t *block_tables, int32_t max_blocks,
@@ -255,7 +264,8 @@ pcr_status pcr_prefix_prefill_attn(const void *q, const pcr_kv_pool *pool,
  * attention) divides a launch among workgroups; a tuning and testing control, not
  * part of the method. Every schedule computes the same result (Sec. 2.2).
  *   PCR_ATTN_SCHEDULE_AUTO (the default): row halves when that still gives at
- *     least two workgroups per compute unit, else key halves; pcr_pipeline_run and
+ *     least two workgroups per compute unit, else key halves, for launches that leave
+ *     compute units idle with the keys cut into chunks; pcr_pipeline_run and
  *     pcr_pipeline_run_offload, whose pull-kernel loads share the compute units
  *     with the attention, take key halves (shorter workgroups let the copy
  *     workgroups onto a compute unit sooner);

@@ -18,6 +18,9 @@
 // Row halves give each workgroup twice the work for one start-up and no merge; the
 // host takes them when the launch still has at least two workgroups per compute
 // unit, key halves otherwise (twice the workgroups for small launches).
+//   key split: key halves with each row tile's keys cut into chunks, one workgroup each,
+//     whose partial results (O, max, sum) a second kernel merges; for launches that
+//     leave compute units idle.
 //
 // Per wave and 64-key tile (4 pool blocks), with v_mfma_f32_32x32x16_bf16:
 //   S^T[key][q] = K Q^T   A = K rows from LDS, B = this wave's Q (registers)
@@ -62,6 +65,7 @@ typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned short u16;
@@ -176,13 +180,51 @@ __device__ __forceinline__ void wait_vmem_keep()
 constexpr int kMaxMapSeqs = 128;
 struct AttnWorkMap {
     int32_t n_seq;                      // slots in use (sequences with new tokens)
-    int32_t per_head;                   // row tiles of all sequences, one kv head
+    int32_t per_head;                   // work items of all sequences, one kv head
+    int32_t chunk;                      // key split: 64-key tiles per item (else unused)
     int32_t seq[kMaxMapSeqs];           // sequence in each slot
-    int32_t tiles_end[kMaxMapSeqs];     // row tiles of the slots up to and including this one
+    int32_t tiles_end[kMaxMapSeqs];     // items of the slots up to and including this one
     int32_t prefix[kMaxMapSeqs];        // the slot's cached tokens p
     int32_t first[kMaxMapSeqs];         // the slot's first new token (row of q and out)
     int32_t count[kMaxMapSeqs];         // the slot's new tokens s
 };
+
+// How a launch divides its work among workgroups (see the head of this file).
+enum AttnMode { kKeyHalves = 0, kRowHalves = 1, kKeySplit = 2 };
+
+// Scratch of key-split launches: kSplitSlots slots of kSplitParts partial results per
+// device, held until the process ends. A launch owns one slot from its claim kernel to
+// the last workgroup of its combine kernel. The slot's owner word is the launch's output
+// pointer, which names the launch: two launches in flight never write one output, so
+// the workgroups find their slot by looking for it, and nothing about it is fixed on the
+// host (launches on any streams and threads, and replays of captured graphs, claim
+// theirs when they run). With every slot taken a launch runs unsplit.
+constexpr int kSplitSlots = 8;
+constexpr int kSplitMinChunk = 4;                        // key tiles of an item, at least
+constexpr int kSplitParts = 256;                         // items of one launch, at most
+constexpr int kSplitPartO = kRowsPerWG * 128 * 4;        // bytes: O of 128 rows x 128 dims, fp32
+constexpr int kSplitPartML = kRowsPerWG * 2 * 8;         // bytes: (max, sum) per lane of 4 waves
+struct SplitControl {
+    unsigned long long owner[kSplitSlots];               // output pointer of the owning launch, 0: free
+    unsigned int done[kSplitSlots];                      // combine workgroups that are through
+};
+__device__ SplitControl split_control;
+__device__ __attribute__((aligned(1024))) char split_o[kSplitSlots][kSplitParts][kSplitPartO];
+__device__ __attribute__((aligned(1024))) char split_ml[kSplitSlots][kSplitParts][kSplitPartML];
+
+// The slot owned by the launch with this output (wave-uniform), or -1.
+__device__ __forceinline__ int split_slot(const u16 *out)
+{
+    const int lane = threadIdx.x & 63;
+    const unsigned long long own =
+        lane < kSplitSlots ? __hip_atomic_load(&split_control.owner[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                           : 0ull;
+    const uint64_t mine = __builtin_amdgcn_ballot_w64(own == (unsigned long long)(uintptr_t)out);
+    return mine ? (int)__builtin_ctzll(mine) : -1;
+}
+
+// 64-key tiles of the keys [0, last].
+__device__ __host__ __forceinline__ int key_tiles(int last) { return last / kTileKeys + 1; }
 
 // A sequence with one new token in a prefill launch (a decode row, Sec. 2.2; prefill
 // and decode rows in one pass, Sec. 4.3): its G rows would fill G columns of the
@@ -193,21 +235,23 @@ struct AttnWorkMap {
 // merge their (O, max, sum) through LDS. The work is then bound by reading K/V, and
 // it overlaps the matrix-bound workgroups of the prefill rows on the other compute
 // units.
+// Keys [n0, n_keys) of the row; with part_o they leave the unnormalised O, max and sum
+// there (a chunk of a key-split launch), otherwise the row is written.
 template <int D>
 __device__ __forceinline__ void decode_workgroup(const u16 *__restrict__ q, const u16 *__restrict__ pool_k,
                                                  const u16 *__restrict__ pool_v, int32_t num_blocks, int32_t Hkv,
                                                  const int32_t *__restrict__ bt_row, int32_t max_blocks, int g, int G,
-                                                 int32_t Hq, int p, int64_t t0, float scale_log2,
-                                                 u16 *__restrict__ out, char *lds)
+                                                 int32_t Hq, int n0, int n_keys, int64_t t0, float scale_log2,
+                                                 u16 *__restrict__ out, char *lds, f32x4 *part_out,
+                                                 float *part_out_ml)
 {
     constexpr int MT = D / 16;
     constexpr int kWaves = kThreads / 64;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int n_keys = p + 1;                       // keys 0 .. p: the row's causal range
-    const int chunk = ((n_keys + kWaves - 1) / kWaves + decode_wave::kStepKeys - 1) / decode_wave::kStepKeys *
+    const int chunk = ((n_keys - n0 + kWaves - 1) / kWaves + decode_wave::kStepKeys - 1) / decode_wave::kStepKeys *
                       decode_wave::kStepKeys;
-    const int kbeg = wave * chunk;
+    const int kbeg = n0 + wave * chunk;
     const int kend = min(n_keys, kbeg + chunk);
     const int last_blk = max(0, min((n_keys - 1) >> 4, max_blocks - 1));
     const int c = lane & 15, q4 = lane >> 4;
@@ -251,7 +295,12 @@ __device__ __forceinline__ void decode_workgroup(const u16 *__restrict__ q, cons
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) o[mt] += a * part_o[(w * MT + mt) * 64 + lane];
         }
-        if (col) {
+        if (part_out) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) part_out[mt * 64 + lane] = o[mt];
+            part_out_ml[2 * lane] = M;
+            part_out_ml[2 * lane + 1] = l_tot;
+        } else if (col) {
             const float inv = 1.f / l_tot;
             u16 *orow = out + (t0 * Hq + h) * D + 4 * q4;
 #pragma unroll
@@ -263,7 +312,58 @@ __device__ __forceinline__ void decode_workgroup(const u16 *__restrict__ q, cons
     }
 }
 
-template <int D, bool ROWS>
+// One work item of a launch.
+struct Item {
+    int g, j;             // kv head and the item's index in the work map (g >= Hkv: none)
+    int b, p, t0, s;      // sequence, cached tokens, first new token, new tokens
+    int local;            // item within the sequence, counted from the sequence's last
+};
+
+// XCD-aware order: workgroup L runs on XCD L % 8. The row tiles of one (sequence,
+// kv head), which read the same K/V, go to workgroups of one XCD and share its L2.
+// With Hkv a multiple of 8, XCD x takes kv heads x, x+8, ... of every sequence, so the
+// eight XCDs get equal work.
+__device__ __forceinline__ Item locate_item(const AttnWorkMap &wm, int32_t Hkv)
+{
+    const int lane = threadIdx.x & 63;
+    Item it;
+    const int x = (int)(blockIdx.x % kXcds), i = (int)(blockIdx.x / kXcds);
+    const int per_xcd = (int)(gridDim.x / kXcds);
+    if (Hkv % kXcds == 0) {
+        const int hh = i / wm.per_head;
+        it.g = x + kXcds * hh;
+        it.j = i - hh * wm.per_head;
+    } else {
+        const int w = x * per_xcd + i;
+        it.g = w / wm.per_head;
+        it.j = w - it.g * wm.per_head;
+    }
+    // Slot of item j: the number of slots whose items end at or before j. Lane l
+    // reads slots l and l + 64 (all fields at once); the slot's fields are then taken
+    // from the lane that holds them.
+    int e[2], fs[2], fp[2], ft[2], fc[2];
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf) {
+        const int k = lane + 64 * hf;
+        const bool in = k < wm.n_seq;
+        e[hf] = in ? wm.tiles_end[k] : INT32_MAX;
+        fs[hf] = in ? wm.seq[k] : 0;
+        fp[hf] = in ? wm.prefix[k] : 0;
+        ft[hf] = in ? wm.first[k] : 0;
+        fc[hf] = in ? wm.count[k] : 0;
+    }
+    const int slot = __builtin_popcountll(__builtin_amdgcn_ballot_w64(e[0] <= it.j)) +
+                     __builtin_popcountll(__builtin_amdgcn_ballot_w64(e[1] <= it.j));
+    const int hf = slot >> 6, sl = slot & 63;
+    it.b = __builtin_amdgcn_readlane(hf ? fs[1] : fs[0], sl);
+    it.p = __builtin_amdgcn_readlane(hf ? fp[1] : fp[0], sl);
+    it.t0 = __builtin_amdgcn_readlane(hf ? ft[1] : ft[0], sl);
+    it.s = __builtin_amdgcn_readlane(hf ? fc[1] : fc[0], sl);
+    it.local = __builtin_amdgcn_readlane(hf ? e[1] : e[0], sl) - 1 - it.j;
+    return it;
+}
+
+template <int D, int MODE>
 __global__ __launch_bounds__(kThreads) void prefill_attn_kernel(
     const u16 *__restrict__ q, const u16 *__restrict__ pool_k, const u16 *__restrict__ pool_v,
     int32_t num_blocks, int32_t Hkv, const int32_t *__restrict__ block_tables, int32_t max_blocks, int32_t Hq,
@@ -277,6 +377,7 @@ __global__ __launch_bounds__(kThreads) void prefill_attn_kernel(
     constexpr int kSlabs = (int)(kPayloadBytes / 1024);       // 1 KB slabs per payload
     static_assert(kGroupWaves % kSlabs == 0, "slab-to-wave mapping");
     constexpr int kKLoads = Geo::KLOADS, kVLoads = Geo::VLOADS;
+    constexpr bool ROWS = MODE == kRowHalves;
     constexpr int RPW = ROWS ? 2 * kRowsPerWG : kRowsPerWG;   // packed rows per workgroup
 
     // Per group: K buffers 0/1 then V buffers 0/1 (double-buffered, tile j in buffer j&1);
@@ -284,48 +385,20 @@ __global__ __launch_bounds__(kThreads) void prefill_attn_kernel(
     // at the end of key halves.
     __shared__ __attribute__((aligned(1024))) char lds[2][2 * (Geo::KBYTES + Geo::VBYTES)];
 
-    // XCD-aware order: workgroup L runs on XCD L % 8. The row tiles of one (sequence,
-    // kv head), which read the same K/V, go to workgroups of one XCD and share its L2.
-    // With the work map and Hkv a multiple of 8, XCD x takes kv heads x, x+8, ... of
-    // every sequence, so the eight XCDs get equal work.
     const int tid = threadIdx.x, lane = tid & 63;
-    int b, g, rt, p, t0, s;
-    {
-        const int x = (int)(blockIdx.x % kXcds), i = (int)(blockIdx.x / kXcds);
-        const int per_xcd = (int)(gridDim.x / kXcds);
-        int j;
-        if (Hkv % kXcds == 0) {
-            const int hh = i / wm.per_head;
-            g = x + kXcds * hh;
-            j = i - hh * wm.per_head;
-        } else {
-            const int w = x * per_xcd + i;
-            g = w / wm.per_head;
-            j = w - g * wm.per_head;
-        }
-        if (g >= Hkv) return;
-        // Slot of row tile j: the number of slots whose tiles end at or before j. Lane l
-        // reads slots l and l + 64 (all fields at once); the slot's fields are then taken
-        // from the lane that holds them.
-        int e[2], fs[2], fp[2], ft[2], fc[2];
-#pragma unroll
-        for (int hf = 0; hf < 2; ++hf) {
-            const int k = lane + 64 * hf;
-            const bool in = k < wm.n_seq;
-            e[hf] = in ? wm.tiles_end[k] : INT32_MAX;
-            fs[hf] = in ? wm.seq[k] : 0;
-            fp[hf] = in ? wm.prefix[k] : 0;
-            ft[hf] = in ? wm.first[k] : 0;
-            fc[hf] = in ? wm.count[k] : 0;
-        }
-        const int slot = __builtin_popcountll(__builtin_amdgcn_ballot_w64(e[0] <= j)) +
-                         __builtin_popcountll(__builtin_amdgcn_ballot_w64(e[1] <= j));
-        const int hf = slot >> 6, sl = slot & 63;
-        b = __builtin_amdgcn_readlane(hf ? fs[1] : fs[0], sl);
-        p = __builtin_amdgcn_readlane(hf ? fp[1] : fp[0], sl);
-        t0 = __builtin_amdgcn_readlane(hf ? ft[1] : ft[0], sl);
-        s = __builtin_amdgcn_readlane(hf ? fc[1] : fc[0], sl);
-        rt = __builtin_amdgcn_readlane(hf ? e[1] : e[0], sl) - 1 - j;
+    const Item it = locate_item(wm, Hkv);
+    const int g = it.g;
+    if (g >= Hkv) return;
+    const int b = it.b, p = it.p, t0 = it.t0, s = it.s;
+    // Key split: item `local` of the sequence is chunk sp of row tile rt.
+    int rt = it.local, sp = 0, part = -1;
+    if constexpr (MODE == kKeySplit) {
+        const int ns = (key_tiles(p + s - 1) + wm.chunk - 1) / wm.chunk;
+        rt = it.local / ns;
+        sp = it.local - rt * ns;
+        const int slot = split_slot(out);
+        if (slot < 0 && sp > 0) return;              // unsplit: chunk 0 takes every key
+        if (slot >= 0) part = slot * kSplitParts + g * wm.per_head + it.j;
     }
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int grp = wave >> 2;              // key halves: which half of the keys; row halves: of the rows
@@ -338,9 +411,20 @@ __global__ __launch_bounds__(kThreads) void prefill_attn_kernel(
     if (s <= 0 || row0 >= rows_total || T <= 0) return;   // uniform over the workgroup
     if (s == 1 && G <= decode_wave::kMaxCols) {           // a decode row (uniform too)
         static_assert(kThreads / 64 * (D / 16) * 64 * 16 + kThreads / 64 * 64 * 8 <= (int)sizeof(lds), "merge area");
-        if (t0 < T)
-            decode_workgroup<D>(q, pool_k, pool_v, num_blocks, Hkv, block_tables + (int64_t)b * max_blocks,
-                                max_blocks, g, G, Hq, p, t0, scale_log2, out, &lds[0][0]);
+        if (t0 >= T) return;
+        int n0 = 0, n_keys = p + 1;                  // keys 0 .. p: the row's causal range
+        f32x4 *po = nullptr;
+        float *pml = nullptr;
+        if constexpr (MODE == kKeySplit) {
+            if (part >= 0 && n_keys > wm.chunk * kTileKeys) {
+                n0 = sp * wm.chunk * kTileKeys;
+                n_keys = min(n_keys, n0 + wm.chunk * kTileKeys);
+                po = reinterpret_cast<f32x4 *>(&split_o[0][0][0] + (int64_t)part * kSplitPartO);
+                pml = reinterpret_cast<float *>(&split_ml[0][0][0] + (int64_t)part * kSplitPartML);
+            }
+        }
+        decode_workgroup<D>(q, pool_k, pool_v, num_blocks, Hkv, block_tables + (int64_t)b * max_blocks, max_blocks,
+                            g, G, Hq, n0, n_keys, t0, scale_log2, out, &lds[0][0], po, pml);
         return;
     }
     const int total = p + s;
@@ -356,12 +440,22 @@ __global__ __launch_bounds__(kThreads) void prefill_attn_kernel(
     const int64_t tq = (int64_t)t0 + i;
 
     const int wg_last = min(rows_total - 1, row0 + RPW - 1);
-    const int ntiles = (p + wg_last / G) / kTileKeys + 1;
-    // key halves: group 0 takes tiles [0, split), group 1 [split, ntiles); row halves:
+    const int all_tiles = key_tiles(p + wg_last / G);
+    // This workgroup's tiles [t_lo, t_lo + ntiles): all, or a chunk of a key split.
+    int t_lo = 0, ntiles = all_tiles;
+    if constexpr (MODE == kKeySplit) {
+        if (part >= 0) {
+            t_lo = sp * wm.chunk;
+            ntiles = min(all_tiles - t_lo, wm.chunk);
+            if (ntiles <= 0) return;                 // (an earlier row tile ends before this chunk)
+            if (all_tiles <= wm.chunk) part = -1;    // the only chunk of its row tile: written directly
+        }
+    }
+    // key halves: group 0 takes the first `split` tiles, group 1 the rest; row halves:
     // both take every tile
     const int split = ROWS ? ntiles : (ntiles + 1) >> 1;
-    const int tile_begin = (!ROWS && grp) ? split : 0;
-    const int n = (ROWS || !grp ? split : ntiles) - tile_begin;   // this group's tiles
+    const int tile_begin = t_lo + ((!ROWS && grp) ? split : 0);
+    const int n = (ROWS || !grp) ? split : ntiles - split;        // this group's tiles
     const int w_first = min(rows_total - 1, wrow0);
     const int w_min_limit = p + w_first / G;
     const int valid_blocks = min((total + kBlockSize - 1) / kBlockSize, max_blocks);
@@ -824,6 +918,29 @@ __global__ __launch_bounds__(kThreads) void prefill_attn_kernel(
     const float mm = fmaxf(m0, m1);
     const float a0 = (m0 == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((m0 - mm) * scale_log2);
     const float a1 = (m1 == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((m1 - mm) * scale_log2);
+    if constexpr (MODE == kKeySplit) {
+        if (part >= 0) {
+            // A chunk's partial result, in the lane layout (1 KB per wave-wide store).
+            if (row_valid && tq < T) {
+                f32x4 *po = reinterpret_cast<f32x4 *>(&split_o[0][0][0] + (int64_t)part * kSplitPartO) +
+                            wg * MT * 4 * 64 + lane;
+                f32x2 *pml = reinterpret_cast<f32x2 *>(&split_ml[0][0][0] + (int64_t)part * kSplitPartML) +
+                             wg * 64 + lane;
+#pragma unroll
+                for (int k = 0; k < MH; ++k)
+#pragma unroll
+                    for (int r4 = 0; r4 < 4; ++r4) {
+                        const f32x4 o1 = xi[(k * 4 + r4) * 64 + lane];
+                        f32x4 v;
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) v[c] = a0 * o_acc[my0 + k][4 * r4 + c] + a1 * o1[c];
+                        po[((my0 + k) * 4 + r4) * 64] = v;
+                    }
+                if (grp == 0) *pml = f32x2{mm, a0 * l_tot + a1 * l1};
+            }
+            return;
+        }
+    }
     const float inv = 1.f / (a0 * l_tot + a1 * l1);
     if (row_valid && tq < T) {
         u16 *orow = out + (tq * Hq + h) * D;
@@ -842,6 +959,124 @@ __global__ __launch_bounds__(kThreads) void prefill_attn_kernel(
     }
 }
 
+// One wave: takes a free slot for the launch with this output (none free: the launch
+// finds no slot and runs unsplit).
+__global__ __launch_bounds__(64) void split_claim_kernel(u16 *out)
+{
+    if (threadIdx.x != 0) return;
+    for (int i = 0; i < kSplitSlots; ++i) {
+        unsigned long long free_word = 0ull;
+        if (__hip_atomic_compare_exchange_strong(&split_control.owner[i], &free_word,
+                                                 (unsigned long long)(uintptr_t)out, __ATOMIC_ACQUIRE,
+                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            return;
+    }
+}
+
+// Merges the chunks of every row tile and decode row of a key-split launch:
+// out = sum_s 2^(c (m_s - M)) O_s / sum_s 2^(c (m_s - M)) l_s with M = max_s m_s. Grid and
+// item order are the split kernel's. The pieces of one row tile (a wave's 32 rows x 8
+// dims) are dealt to the waves of all its chunks' workgroups, so the reads of the
+// partial results, which bound this kernel, come from every compute unit.
+constexpr int kCombineThreads = 512;
+template <int D>
+__global__ __launch_bounds__(kCombineThreads) void split_combine_kernel(int32_t Hkv, int32_t Hq, int32_t T,
+                                                                        float scale_log2, u16 *__restrict__ out,
+                                                                        const AttnWorkMap wm)
+{
+    constexpr int MT = D / 32;
+    constexpr int kCombineWaves = kCombineThreads / 64;
+    const int slot = split_slot(out);
+    if (slot < 0) return;                            // ran unsplit
+    const Item it = locate_item(wm, Hkv);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int G = Hq / Hkv;
+    if (it.g < Hkv) {
+        const int p = it.p, s = it.s, rows_total = s * G;
+        const int ns_seq = (key_tiles(p + s - 1) + wm.chunk - 1) / wm.chunk;
+        const int rt = it.local / ns_seq, sp = it.local - rt * ns_seq;
+        const int row0 = rt * kRowsPerWG;
+        const bool decode_row = s == 1 && G <= decode_wave::kMaxCols;
+        const int wg_last = min(rows_total - 1, row0 + kRowsPerWG - 1);
+        const int ns = (key_tiles(p + wg_last / G) + wm.chunk - 1) / wm.chunk;   // chunks of this row tile
+        // chunk s of the row tile is item j + sp - s (items count down)
+        const int64_t part0 = (int64_t)slot * kSplitParts + it.g * wm.per_head + it.j + sp;
+        const f32x4 *po = reinterpret_cast<const f32x4 *>(&split_o[0][0][0]);
+        const f32x2 *pml = reinterpret_cast<const f32x2 *>(&split_ml[0][0][0]);
+        const int waves = (wg_last - row0) / kRowsPerWave + 1;   // of the row tile, with rows
+        const int pieces = ns <= 1 || row0 >= rows_total ? 0 : decode_row ? D / 16 : waves * MT * 4;
+        const float c = decode_row ? 1.f : scale_log2;    // a decode row's max is scaled already
+        for (int pc = sp * kCombineWaves + wave; pc < pieces; pc += ns_seq * kCombineWaves) {
+            const int wg = decode_row ? 0 : pc / (MT * 4);
+            int64_t tq;
+            int h, d0;
+            bool ok;
+            if (decode_row) {                        // piece = 16 dims; lane = head lane % 16, dims 4 (lane / 16) ..
+                h = it.g * G + (lane & 15);
+                tq = it.t0;
+                d0 = 16 * pc + 4 * (lane >> 4);
+                ok = (lane & 15) < G;
+            } else {                                 // piece = (wave, 8 dims); lane = row lane % 32, half lane / 32
+                const int R = row0 + wg * kRowsPerWave + (lane & 31);
+                const int kr = pc - wg * MT * 4;
+                h = it.g * G + R % G;
+                tq = (int64_t)it.t0 + R / G;
+                d0 = 8 * kr + 4 * (lane >> 5);
+                ok = R < rows_total;
+            }
+            if (!ok || tq >= T) continue;            // (lanes without a row)
+            // W chunks per pass, their loads in flight together (a chunk past the last is
+            // reread with weight 0); the running sums are rescaled between passes.
+            float M = -INFINITY, L = 0.f;
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+            auto merge = [&](auto width) __attribute__((always_inline)) {
+                constexpr int W = decltype(width)::value;
+                for (int k0 = 0; k0 < ns; k0 += W) {
+                    f32x2 ml[W];
+                    f32x4 o[W];
+#pragma unroll
+                    for (int i = 0; i < W; ++i) {
+                        const int64_t pt = part0 - min(k0 + i, ns - 1);
+                        ml[i] = pml[pt * (kSplitPartML / 8) + wg * 64 + lane];
+                        o[i] = po[pt * (kSplitPartO / 16) + pc * 64 + lane];
+                    }
+                    float Mn = M;                    // finite from the first pass: chunk 0 has keys of every row
+#pragma unroll
+                    for (int i = 0; i < W; ++i) Mn = fmaxf(Mn, ml[i][0]);
+                    const float r = __builtin_amdgcn_exp2f((M - Mn) * c);   // 0 on the first pass
+                    M = Mn;
+                    L *= r;
+                    acc *= r;
+#pragma unroll
+                    for (int i = 0; i < W; ++i) {
+                        const float w = k0 + i < ns ? __builtin_amdgcn_exp2f((ml[i][0] - M) * c) : 0.f;
+                        L += w * ml[i][1];
+                        acc += w * o[i];
+                    }
+                }
+            };
+            if (ns <= 4) merge(std::integral_constant<int, 4>{});
+            else merge(std::integral_constant<int, 16>{});
+            const bf16x4 bv = __builtin_convertvector(acc * (1.f / L), bf16x4);
+            *reinterpret_cast<u32x2 *>(out + (tq * Hq + h) * D + d0) = __builtin_bit_cast(u32x2, bv);
+        }
+    }
+    // The last workgroup gives the slot back (every workgroup has looked it up and read
+    // its partial results by then).
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        // Relaxed: this kernel only reads the slot, and every read has returned its value
+        // before the barrier; the words below order themselves through the counter.
+        const unsigned before = __hip_atomic_fetch_add(&split_control.done[slot], 1u, __ATOMIC_RELAXED,
+                                                       __HIP_MEMORY_SCOPE_AGENT);
+        if (before + 1 == gridDim.x) {
+            __hip_atomic_store(&split_control.done[slot], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&split_control.owner[slot], 0ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+}
+
 }  // namespace
 
 int attn_rows_per_workgroup(int) { return kRowsPerWG; }
@@ -850,14 +1085,54 @@ namespace {
 // Schedule override (pcr_prefill_attn_set_schedule): 0 chooses per launch.
 std::atomic<int> g_schedule{PCR_ATTN_SCHEDULE_AUTO};
 
-template <int D, bool ROWS>
+template <int D, int MODE>
 void launch_attn(dim3 grid, hipStream_t s, const u16 *qq, const u16 *pk, const u16 *pv, const pcr_kv_pool &pool,
                  const int32_t *block_tables, int32_t max_blocks, int32_t num_q_heads, int32_t T, float scale_log2,
                  float rescale_thr, u16 *oo, const AttnWorkMap &wm)
 {
-    hipLaunchKernelGGL((prefill_attn_kernel<D, ROWS>), grid, dim3(kThreads), 0, s, qq, pk, pv, pool.num_blocks,
+    hipLaunchKernelGGL((prefill_attn_kernel<D, MODE>), grid, dim3(kThreads), 0, s, qq, pk, pv, pool.num_blocks,
                        pool.num_kv_heads, block_tables, max_blocks, num_q_heads, T, scale_log2, rescale_thr, oo,
                        wm);
+}
+
+// Key split of a key-halves launch: the key tiles of an item, or 0 for none. A launch of
+// few workgroups (a short suffix on a long prefix, one GPU's share of the heads) leaves
+// compute units idle while each workgroup walks every key; cutting the row tiles' keys
+// into chunks gives each compute unit one item. The chunk is the smallest one whose
+// items still fit the compute units (and the scratch) in one round.
+// A key tile takes a workgroup 0.58 us with few compute units busy and 0.75-0.9 us with
+// all of them (the clock follows the power); the claim, the partial results and the
+// combine kernel together cost about 12 us, i.e. 20 tiles. So the split is taken when
+// the longest item has at least 4/3 chunk + 20 tiles. Measured (32 query / 8 kv heads of
+// 128, unsplit -> split): 43 new tokens on 7985 cached 77 -> 25 us; 16 on 2000 25.3 ->
+// 18; 128 on 4000 44.5 -> 27; 400 on 4000 47.4 -> 44; 2 on 16000 143 -> 26; 1024 on 15360
+// twice with 8 / 1 heads 150 -> 127. Near the line: 16 on 1300 19.5 -> 18.5, 512 on 4000
+// 48.5 -> 48.6 us. (Chunks of at least 4, 6, 8, 12 or 16 tiles: 4 to 8 alike, 12 and 16
+// up to 20% slower on prefixes of 2k.)
+int32_t split_chunk(const int32_t *seq, int n, const int32_t *host_prefix_lens, const int32_t *host_cu_suffix, int G,
+                    int Hkv, int n_cu)
+{
+    const int64_t cap = std::min(n_cu, kSplitParts);
+    int32_t longest = 0;
+    for (int k = 0; k < n; ++k)
+        longest = std::max(longest, key_tiles(host_prefix_lens[seq[k]] + host_cu_suffix[seq[k] + 1] -
+                                              host_cu_suffix[seq[k]] - 1));
+    auto items = [&](int32_t c) {
+        int64_t w = 0;
+        for (int k = 0; k < n; ++k) {
+            const int32_t b = seq[k], sb = host_cu_suffix[b + 1] - host_cu_suffix[b];
+            w += ((int64_t)sb * G + kRowsPerWG - 1) / kRowsPerWG *
+                 ((key_tiles(host_prefix_lens[b] + sb - 1) + c - 1) / c);
+        }
+        return w * Hkv;
+    };
+    int32_t lo = kSplitMinChunk, hi = (longest - 20) * 3 / 4;
+    if (lo > hi || items(hi) > cap) return 0;
+    while (lo < hi) {
+        const int32_t mid = lo + (hi - lo) / 2;
+        if (items(mid) <= cap) hi = mid; else lo = mid + 1;
+    }
+    return hi;
 }
 
 // One launch over the sequences seq[0..n) (each with new tokens, n <= kMaxMapSeqs,
@@ -865,7 +1140,7 @@ void launch_attn(dim3 grid, hipStream_t s, const u16 *qq, const u16 *pk, const u
 hipError_t launch_group(const int32_t *seq, int n, const u16 *qq, const pcr_kv_pool &pool,
                         const int32_t *block_tables, int32_t max_blocks, const int32_t *host_prefix_lens,
                         const int32_t *host_cu_suffix, int32_t num_q_heads, int32_t T, float scale_log2,
-                        float rescale_thr, u16 *oo, hipStream_t s, int auto_schedule, int n_cu)
+                        float rescale_thr, u16 *oo, hipStream_t s, int auto_schedule, int n_cu, bool can_split)
 {
     const int Hkv = pool.num_kv_heads, G = num_q_heads / Hkv;
     auto rows_of = [&](int32_t b) { return ((int64_t)host_cu_suffix[b + 1] - host_cu_suffix[b]) * G; };
@@ -880,7 +1155,16 @@ hipError_t launch_group(const int32_t *seq, int n, const u16 *qq, const pcr_kv_p
     const bool rows = sched == PCR_ATTN_SCHEDULE_ROW_HALVES ||
                       (sched == PCR_ATTN_SCHEDULE_AUTO && tiles_rows * Hkv >= 2 * (int64_t)n_cu);
     const int64_t rpw = rows ? 2 * kRowsPerWG : kRowsPerWG;
-    auto tiles_of = [&](int32_t b) { return (rows_of(b) + rpw - 1) / rpw; };
+    // Key tiles per item, 0: no key split.
+    const int32_t chunk =
+        sched == PCR_ATTN_SCHEDULE_AUTO && !rows && can_split
+            ? split_chunk(seq, n, host_prefix_lens, host_cu_suffix, G, Hkv, n_cu)
+            : 0;
+    auto keys_of = [&](int32_t b) { return host_prefix_lens[b] + host_cu_suffix[b + 1] - host_cu_suffix[b]; };
+    auto tiles_of = [&](int32_t b) {
+        const int64_t t = (rows_of(b) + rpw - 1) / rpw;
+        return chunk ? t * ((key_tiles(keys_of(b) - 1) + chunk - 1) / chunk) : t;
+    };
 
     // Slot order: the given order (longest context first), with the decode rows (one
     // new token, one workgroup each, bound by HBM) spread evenly over the prefill
@@ -920,25 +1204,30 @@ hipError_t launch_group(const int32_t *seq, int n, const u16 *qq, const pcr_kv_p
     }
     wm.n_seq = n;
     wm.per_head = cum;
+    wm.chunk = chunk;
     const int64_t n_items = (Hkv % kXcds == 0) ? (int64_t)cum * Hkv : ((int64_t)cum * Hkv + kXcds - 1) / kXcds * kXcds;
     const dim3 grid((unsigned)n_items);
     auto *pk = static_cast<const u16 *>(pool.k);
     auto *pv = static_cast<const u16 *>(pool.v);
-    if (pool.head_dim == 128) {
-        if (rows)
-            launch_attn<128, true>(grid, s, qq, pk, pv, pool, block_tables, max_blocks, num_q_heads, T, scale_log2,
-                                   rescale_thr, oo, wm);
-        else
-            launch_attn<128, false>(grid, s, qq, pk, pv, pool, block_tables, max_blocks, num_q_heads, T, scale_log2,
-                                    rescale_thr, oo, wm);
-    } else {
-        if (rows)
-            launch_attn<64, true>(grid, s, qq, pk, pv, pool, block_tables, max_blocks, num_q_heads, T, scale_log2,
-                                  rescale_thr, oo, wm);
-        else
-            launch_attn<64, false>(grid, s, qq, pk, pv, pool, block_tables, max_blocks, num_q_heads, T, scale_log2,
-                                   rescale_thr, oo, wm);
-    }
+    auto launch = [&](auto dim) {
+        constexpr int D = decltype(dim)::value;
+        auto attn = [&](auto mode) {
+            launch_attn<D, decltype(mode)::value>(grid, s, qq, pk, pv, pool, block_tables, max_blocks, num_q_heads,
+                                                  T, scale_log2, rescale_thr, oo, wm);
+        };
+        if (rows) {
+            attn(std::integral_constant<int, kRowHalves>{});
+        } else if (!chunk) {
+            attn(std::integral_constant<int, kKeyHalves>{});
+        } else {
+            hipLaunchKernelGGL(split_claim_kernel, dim3(1), dim3(64), 0, s, oo);
+            attn(std::integral_constant<int, kKeySplit>{});
+            hipLaunchKernelGGL((split_combine_kernel<D>), grid, dim3(kCombineThreads), 0, s, Hkv, num_q_heads, T,
+                               scale_log2, oo, wm);
+        }
+    };
+    if (pool.head_dim == 128) launch(std::integral_constant<int, 128>{});
+    else launch(std::integral_constant<int, 64>{});
     return hipGetLastError();
 }
 }  // namespace
@@ -969,12 +1258,17 @@ hipError_t launch_prefix_prefill_attn(const void *q, const pcr_kv_pool &pool,
     const int n_act = (int)seq.size();
     const int n_launch = (n_act + kMaxMapSeqs - 1) / kMaxMapSeqs;
     int32_t group[kMaxMapSeqs];
+    // A key-split launch's chunks read q until its combine kernel writes out, and its rows
+    // that need no merge are written beside them: not for outputs that overlap q.
+    const uintptr_t qa = (uintptr_t)q, oa = (uintptr_t)out;
+    const uintptr_t bytes = (uintptr_t)T * num_q_heads * pool.head_dim * 2;
+    const bool can_split = n_launch == 1 && (qa + bytes <= oa || oa + bytes <= qa);
     for (int l = 0; l < n_launch; ++l) {
         int n = 0;
         for (int k = l; k < n_act; k += n_launch) group[n++] = seq[k];
         const hipError_t e = launch_group(group, n, qq, pool, block_tables, max_blocks, host_prefix_lens,
                                           host_cu_suffix, num_q_heads, T, scale_log2, rescale_thr, oo, s,
-                                          auto_schedule, n_cu);
+                                          auto_schedule, n_cu, can_split);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -1,0 +1,136 @@
+"""GPU: prefill launches of few workgroups, whose row tiles' keys are cut into chunks and
+merged by a second kernel (the default schedule's choice for a short suffix on a long
+prefix), against the fp64 oracle; from captured graphs; on many streams at once; and not
+taken for an output that is the query buffer."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import attention as oattn
+from oracle import datamove as odm
+from paper_2603_23049_amd import pcr, synth
+from gpuio import GpuLayer, MAX_ABS, MEAN_ABS, attn_schedule, error_stats, say, u16
+
+pytestmark = pytest.mark.gpu
+BS = 16
+
+
+def _layer(pl, sl, G, Hkv, d, seed):
+    nb = sum(-(-(p + s) // BS) for p, s in zip(pl, sl)) + 3
+    b = synth.ragged_batch("split", Hq=Hkv * G, Hkv=Hkv, d=d, prefix_lens=pl, suffix_lens=sl, pool_blocks=nb, seed=seed)
+    data = synth.make_layer(b)
+    rng = np.random.Generator(np.random.PCG64(seed + 1))
+    shape = (nb, Hkv, BS * d)
+    # (the slots no token fills hold NaN patterns: nothing past a sequence may reach the result)
+    pk0, pv0 = np.full(shape, 0xFFFF, np.uint16), np.full(shape, 0xFFFF, np.uint16)
+    L = GpuLayer(b, data, pk0, pv0)
+    L.load("kernel_pull")
+    L.append()
+    torch.cuda.synchronize()
+    # a partial last prefix block is loaded whole; the tokens past the sequence get the NaN back
+    plan = odm.plan(b.prefix_lens, b.suffix_lens, b.block_tables, b.host_blocks, BS)
+    pk, pv = odm.pool_after_layer(pk0, pv0, data.host_k, data.host_v, plan, data.k_new, data.v_new, BS)
+    flat = np.arange(0, b.T * b.num_q_heads, max(1, b.T * b.num_q_heads // 1500))
+    rows = np.stack([flat // b.num_q_heads, flat % b.num_q_heads], 1).astype(np.int32)
+    want = oattn.attention(data.q, pk, pv, b.block_tables, np.asarray(pl, np.int32), plan[3], Hkv, BS, rows=rows)
+    return L, rows, want
+
+
+def _check(L, rows, want, label):
+    got = L.out_f64()
+    assert np.all(np.isfinite(got)), label
+    mx, mean = error_stats(got[rows[:, 0], rows[:, 1]], want)
+    say(f"    {label}: max_abs={mx:.3e} mean_abs={mean:.3e}")
+    assert mx <= MAX_ABS and mean <= MEAN_ABS, f"{label}: max {mx} mean {mean}"
+
+
+CASES = [
+    # one row tile, partly filled; last chunk of one key past a tile, a full one, one short of it
+    ([1985], [15], 4, 8, 128), ([1984], [64], 1, 8, 128), ([2031], [1], 4, 8, 128), ([2047], [1], 16, 2, 64),
+    # many chunks: more than one pass of the combine
+    ([9000], [3], 4, 1, 128), ([9000], [1], 5, 1, 64),
+    # row tiles that end chunks before the last one (no prefix), rows past the end of a tile
+    ([0], [2000], 2, 2, 128), ([5], [1999], 1, 3, 64),
+    # a token's heads cut by row tiles; more than 16 heads per kv head: one-token rows on tiles
+    ([3000, 2500], [33, 70], 5, 2, 128), ([3000, 4000], [1, 9], 20, 1, 128),
+    # ragged: sequences of one chunk, of many, decode rows beside them, none new in one
+    ([4000, 100, 2999, 0, 5000, 17], [40, 30, 1, 64, 1, 0], 4, 4, 128),
+    ([3000, 3100, 10, 2600], [1, 1, 1, 1], 8, 8, 64),
+]
+
+
+@pytest.mark.parametrize("pl,sl,G,Hkv,d", CASES)
+def test_split_launch_against_oracle(pl, sl, G, Hkv, d):
+    say(f"[gpu] key split p={pl} s={sl} G={G} Hkv={Hkv} d={d}")
+    L, rows, want = _layer(pl, sl, G, Hkv, d, seed=300 + len(pl) + G + sl[0])
+    L.attn()
+    torch.cuda.synchronize()
+    _check(L, rows, want, "split")
+    first = L.out.clone()
+    L.out.fill_(-1)
+    L.attn()
+    torch.cuda.synchronize()
+    assert torch.equal(L.out, first), "a repeated call differs"
+    with attn_schedule("key_halves"):
+        L.attn()
+    torch.cuda.synchronize()
+    assert not torch.equal(L.out, first), "the default schedule did not split these keys"
+
+
+def test_split_launch_replayed_from_a_graph_beside_eager_calls():
+    L, rows, want = _layer([3000], [20], 4, 8, 128, seed=41)
+    say("[gpu] key split from a graph")
+    L.attn()
+    torch.cuda.synchronize()
+    eager = L.out.clone()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        L.attn()
+    for _ in range(4):
+        L.out.fill_(-1)
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(L.out, eager)
+        L.attn()
+        torch.cuda.synchronize()
+        assert torch.equal(L.out, eager)
+    _check(L, rows, want, "graph")
+
+
+def test_split_launches_on_many_streams():
+    """More streams than the scratch holds launches: whichever launches overlap, every
+    output is right (one that finds the scratch taken runs without chunks), and the
+    scratch is whole again afterwards."""
+    L, rows, want = _layer([5000], [24], 4, 8, 128, seed=43)
+    say("[gpu] key split on 12 streams")
+    L.attn()
+    torch.cuda.synchronize()
+    eager = L.out.clone()
+    streams = [torch.cuda.Stream() for _ in range(12)]
+    outs = [torch.full_like(L.out, -1) for _ in streams]
+    torch.cuda.synchronize()
+    for _ in range(6):
+        for s, o in zip(streams, outs):
+            pcr.prefix_prefill_attn(L.q, L.pool, L.bt, L.pl, L.cu, L.pl_np, L.cu_np, L.batch.num_q_heads, o,
+                                    sm_scale=L.sm_scale, stream=s)
+    torch.cuda.synchronize()
+    for o in outs:
+        L.out.copy_(o)
+        _check(L, rows, want, "stream")
+    L.attn()
+    torch.cuda.synchronize()
+    assert torch.equal(L.out, eager)
+
+
+def test_output_in_place_of_the_queries_is_not_split():
+    """Chunks of one row tile read its queries after others have been written out, so an
+    output that overlaps q takes the launch without chunks."""
+    L, rows, want = _layer([3000], [20], 4, 8, 128, seed=47)
+    with attn_schedule("key_halves"):
+        L.attn()
+    torch.cuda.synchronize()
+    whole = L.out.clone()
+    q = L.q.clone()
+    pcr.prefix_prefill_attn(q, L.pool, L.bt, L.pl, L.cu, L.pl_np, L.cu_np, L.batch.num_q_heads, q, sm_scale=L.sm_scale)
+    torch.cuda.synchronize()
+    assert torch.equal(q.view(torch.int16), whole)
