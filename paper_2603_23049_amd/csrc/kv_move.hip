@@ -13,7 +13,13 @@ namespace {
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned short u16;
 
-constexpr int kTileTokens = 16;
+// Output rows per gather workgroup: 16 and 64 were 2-5% slower on 268 MB, 16 20% on two
+// kv heads.
+constexpr int kGatherTile = 32;
+// Output bytes from which the gather reads K with non-temporal loads: what a call this
+// large reads is not in the caches, and passing them by saved 3-15% of a gather of
+// 163-268 MB; below, it cost 5-10% on data that still was (10-30 MB).
+constexpr int64_t kNtBytes = 64ll << 20;
 // New tokens per append workgroup: 32 measured as fast as 16 on block-aligned slot lists
 // and 31% faster on the RAG mix's (whose tiles start inside chunks); 64 was 3.5% slower
 // on aligned lists of 128k tokens.
@@ -128,47 +134,118 @@ __global__ __launch_bounds__(256) void append_kv_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// gather: grid (ceil(total/16), Hkv), 256 threads; out rows in logical order.
+// gather: grid (ceil(total/TILE), Hkv), 256 threads; out rows in logical order. One
+// workgroup reads TILE output rows of one kv head. K rows are copied 16 B at a time.
+// V is d-major inside a block: each aligned chunk of 8 slots of one dim that the tile's
+// rows use is read by one 16-byte load (two dims per task), its elements go through LDS,
+// and the rows leave it 16 B at a time, with non-temporal stores (whole lines that
+// this kernel does not read again). Bound by moving the bytes: 19897 ragged tokens
+// (163 MB) 58.5 us when V was read by eight 2-byte loads per 16 bytes of output, 39 with
+// whole chunks, 31.4 with the non-temporal stores, 30.5 = 5.3 TB/s with the K loads
+// non-temporal too (NT; V loads stay ordinary: a line's two 16-byte halves are read by
+// different tasks, and bypassing the caches took 41 us); 268 MB of aligned tokens
+// 99.5 -> 45 us = 5.9 TB/s.
+// A row whose block is not in the pool or past the table is written as zeros.
 // ---------------------------------------------------------------------------
-template <int D>
+template <int D, int TILE, bool NT>
 __global__ __launch_bounds__(256) void gather_kv_kernel(
     const u16 *__restrict__ pool_k, const u16 *__restrict__ pool_v, int32_t num_blocks, int32_t Hkv,
     const int32_t *__restrict__ block_tables, int32_t max_blocks,
     const int32_t *__restrict__ starts, const int32_t *__restrict__ cu_out, int32_t B,
     int32_t total, u16 *__restrict__ k_out, u16 *__restrict__ v_out)
 {
-    constexpr int CPR = D / 8;
+    static_assert(TILE <= 64, "one wave ranks the chunk runs");
+    constexpr int CPR = D / 8;                 // 16-B chunks per row
+    constexpr int NCH = (TILE * CPR + 255) / 256;
+    __shared__ __attribute__((aligned(16))) u16 vs[TILE][D + 8];
+    __shared__ int32_t blks[TILE];             // pool block of each row, -1: none
+    __shared__ int32_t offs[TILE];             // slot inside the block
+    __shared__ int32_t runs[TILE];             // (first row << 8) | rows, one per chunk run
+    __shared__ int32_t n_runs;
+
     const int g = blockIdx.y, tid = threadIdx.x;
-    if (tid >= kTileTokens * CPR) return;
-    const int r = blockIdx.x * kTileTokens + tid / CPR, c = tid % CPR;
-    if (r >= total) return;
-    int lo = 0, hi = B - 1;                  // sequence b with cu_out[b] <= r < cu_out[b+1]
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) / 2;
-        if (cu_out[mid] <= r) lo = mid; else hi = mid - 1;
-    }
-    const int b = lo;
-    const int t = starts[b] + (r - cu_out[b]);
-    const int64_t dst = ((int64_t)r * Hkv + g) * D + c * 8;
-    u32x4 kw = {0u, 0u, 0u, 0u}, vw = {0u, 0u, 0u, 0u};
-    const int lb = t / kBlockSize;
-    if (t >= 0 && lb < max_blocks) {
-        const int64_t blk = block_tables[(int64_t)b * max_blocks + lb];
-        const int64_t o = t % kBlockSize;
-        if (blk >= 0 && blk < num_blocks) {
-            kw = *reinterpret_cast<const u32x4 *>(pool_k + ((blk * Hkv + g) * kBlockSize + o) * D + c * 8);
-            const u16 *vb = pool_v + ((blk * Hkv + g) * D + c * 8) * kBlockSize + o;
-            u16 e[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) e[k] = vb[k * kBlockSize];
-            vw.x = e[0] | ((unsigned)e[1] << 16);
-            vw.y = e[2] | ((unsigned)e[3] << 16);
-            vw.z = e[4] | ((unsigned)e[5] << 16);
-            vw.w = e[6] | ((unsigned)e[7] << 16);
+    const int row0 = blockIdx.x * TILE;
+    if (tid < 64) {                            // wave 0: where each row lies, and the chunk runs
+        const int r = row0 + tid;
+        int32_t blk = -1, o = 0;
+        if (tid < TILE && r < total) {
+            int lo = 0, hi = B - 1;            // sequence b with cu_out[b] <= r < cu_out[b+1]
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) / 2;
+                if (cu_out[mid] <= r) lo = mid; else hi = mid - 1;
+            }
+            const int t = starts[lo] + (r - cu_out[lo]);
+            if (t >= 0 && t / kBlockSize < max_blocks) {
+                const int32_t id = block_tables[(int64_t)lo * max_blocks + t / kBlockSize];
+                if (id >= 0 && id < num_blocks) {
+                    blk = id;
+                    o = t % kBlockSize;
+                }
+            }
+        }
+        // A row starts a run when it has a block and opens an aligned chunk of 8 slots or
+        // does not follow the previous row's slot; the run goes on to the next start or
+        // row without a block.
+        const int32_t pb = __shfl_up(blk, 1), po = __shfl_up(o, 1);
+        const bool valid = blk >= 0;
+        const bool start = valid && (tid == 0 || o % 8 == 0 || pb != blk || po != o - 1);
+        const uint64_t starts_m = __builtin_amdgcn_ballot_w64(start);
+        const uint64_t stops = starts_m | ~__builtin_amdgcn_ballot_w64(valid);   // bits past TILE are stops
+        if (start) {
+            const uint64_t after = tid == 63 ? 0ull : stops >> (tid + 1);
+            const int len = after ? 1 + __builtin_ctzll(after) : 64 - tid;
+            runs[__builtin_popcountll(starts_m & ((1ull << tid) - 1ull))] = (tid << 8) | len;
+        }
+        if (tid == 0) n_runs = __builtin_popcountll(starts_m);
+        if (tid < TILE) {
+            blks[tid] = blk;
+            offs[tid] = o;
         }
     }
-    *reinterpret_cast<u32x4 *>(k_out + dst) = kw;
-    *reinterpret_cast<u32x4 *>(v_out + dst) = vw;
+    __syncthreads();
+
+    u32x4 kv[NCH];
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) {
+        const int c = tid + 256 * i, r = c / CPR, cc = c % CPR;
+        kv[i] = u32x4{0u, 0u, 0u, 0u};
+        if (c < TILE * CPR && blks[r] >= 0) {
+            auto *p = reinterpret_cast<const u32x4 *>(
+                pool_k + (((int64_t)blks[r] * Hkv + g) * kBlockSize + offs[r]) * D + cc * 8);
+            if constexpr (NT) kv[i] = __builtin_nontemporal_load(p);
+            else kv[i] = *p;
+        }
+    }
+    // V: task = (run, two dims)
+    const int nr = n_runs;
+    for (int task = tid; task < nr * (D / 2); task += 256) {
+        const int k = task / (D / 2), x = 2 * (task % (D / 2));
+        const int rv = runs[k], r0 = rv >> 8, len = rv & 0xff;
+        const int o = offs[r0];
+        const u16 *src = pool_v + (((int64_t)blks[r0] * Hkv + g) * D + x) * kBlockSize + (o & ~7);
+        const u32x4 a = *reinterpret_cast<const u32x4 *>(src);
+        const u32x4 b = *reinterpret_cast<const u32x4 *>(src + kBlockSize);
+        const int e0 = o & 7;                  // the chunk's element of row r0
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {          // element e of both dims, as one 32-bit word
+            const uint32_t w = e & 1 ? (a[e >> 1] >> 16) | (b[e >> 1] & 0xFFFF0000u)
+                                     : (a[e >> 1] & 0xFFFFu) | (b[e >> 1] << 16);
+            if (len == 8 || (e >= e0 && e < e0 + len)) *reinterpret_cast<uint32_t *>(&vs[r0 + e - e0][x]) = w;
+        }
+    }
+    __syncthreads();
+
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) {
+        const int c = tid + 256 * i, r = c / CPR, cc = c % CPR;
+        if (c < TILE * CPR && row0 + r < total) {
+            const int64_t dst = ((int64_t)(row0 + r) * Hkv + g) * D + cc * 8;
+            u32x4 vv = {0u, 0u, 0u, 0u};
+            if (blks[r] >= 0) vv = *reinterpret_cast<const u32x4 *>(&vs[r][cc * 8]);
+            __builtin_nontemporal_store(kv[i], reinterpret_cast<u32x4 *>(k_out + dst));
+            __builtin_nontemporal_store(vv, reinterpret_cast<u32x4 *>(v_out + dst));
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -242,17 +319,20 @@ hipError_t launch_gather_kv(const pcr_kv_pool &pool, const int32_t *block_tables
                             const int32_t *starts, const int32_t *cu_out, int32_t B, int32_t total,
                             void *k_out, void *v_out, hipStream_t s)
 {
-    const dim3 grid((total + kTileTokens - 1) / kTileTokens, pool.num_kv_heads);
-    auto *pk = static_cast<const u16 *>(pool.k);
-    auto *pv = static_cast<const u16 *>(pool.v);
-    if (pool.head_dim == 128)
-        hipLaunchKernelGGL(gather_kv_kernel<128>, grid, dim3(256), 0, s, pk, pv, pool.num_blocks,
-                           pool.num_kv_heads, block_tables, max_blocks, starts, cu_out, B, total,
-                           static_cast<u16 *>(k_out), static_cast<u16 *>(v_out));
-    else
-        hipLaunchKernelGGL(gather_kv_kernel<64>, grid, dim3(256), 0, s, pk, pv, pool.num_blocks,
-                           pool.num_kv_heads, block_tables, max_blocks, starts, cu_out, B, total,
-                           static_cast<u16 *>(k_out), static_cast<u16 *>(v_out));
+    const dim3 grid((total + kGatherTile - 1) / kGatherTile, pool.num_kv_heads);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, static_cast<const u16 *>(pool.k),
+                           static_cast<const u16 *>(pool.v), pool.num_blocks, pool.num_kv_heads, block_tables,
+                           max_blocks, starts, cu_out, B, total, static_cast<u16 *>(k_out), static_cast<u16 *>(v_out));
+    };
+    const bool nt = 2 * (int64_t)total * pool.num_kv_heads * pool.head_dim * 2 >= kNtBytes;
+    if (pool.head_dim == 128) {
+        if (nt) launch(gather_kv_kernel<128, kGatherTile, true>);
+        else launch(gather_kv_kernel<128, kGatherTile, false>);
+    } else {
+        if (nt) launch(gather_kv_kernel<64, kGatherTile, true>);
+        else launch(gather_kv_kernel<64, kGatherTile, false>);
+    }
     return hipGetLastError();
 }
 

@@ -1,0 +1,74 @@
+"""GPU: gather against plain numpy indexing, bit for bit, where its tiles of 32 rows and
+chunks of 8 slots can go wrong: ranges that start and end inside chunks and blocks, empty
+and one-token sequences, rows whose block is missing, sizes on both sides of the
+non-temporal loads."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2603_23049_amd import pcr, synth
+from gpuio import dev, say, u16
+
+pytestmark = pytest.mark.gpu
+BS = 16
+
+
+def _pool(rng, nb, Hkv, d):
+    shape = (nb, Hkv, BS * d)
+    return synth.normal_bf16(rng, shape), synth.normal_bf16(rng, shape)
+
+
+def _gather_case(starts, lens, Hkv, d, seed, missing=0):
+    rng = np.random.Generator(np.random.PCG64(seed))
+    need = [-(-(max(0, a) + n) // BS) for a, n in zip(starts, lens)]
+    nb = sum(need) + 2
+    pk, pv = _pool(rng, nb, Hkv, d)
+    perm = rng.permutation(nb).astype(np.int32)
+    bt = np.full((len(lens), max(max(need), 1)), -1, np.int32)
+    off = 0
+    for b, n in enumerate(need):
+        bt[b, :n] = perm[off:off + n]
+        off += n
+    for _ in range(missing):                       # ids outside the pool: their rows come back as zeros
+        b = int(rng.integers(len(need)))
+        if need[b]:
+            bt[b, int(rng.integers(need[b]))] = rng.choice([-1, nb, 2**31 - 1])
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    total = int(cu[-1])
+    k_out = torch.full((total, Hkv, d), -1, dtype=torch.int16, device="cuda")
+    v_out = torch.full_like(k_out, -1)
+    pool = pcr.KVPool(dev(pk), dev(pv), Hkv, d)
+    pcr.gather_kv(pool, dev(bt), dev(np.asarray(starts, np.int32)), dev(cu), total, k_out, v_out)
+    torch.cuda.synchronize()
+    t = np.concatenate([np.arange(a, a + n) for a, n in zip(starts, lens)]).astype(np.int64)
+    b = np.repeat(np.arange(len(lens)), lens)
+    inside = (t >= 0) & (t // BS < bt.shape[1])
+    blk = np.where(inside, bt[b, np.clip(t // BS, 0, bt.shape[1] - 1)], -1).astype(np.int64)
+    ok = (blk >= 0) & (blk < nb)
+    blk0, o = np.where(ok, blk, 0), t % BS
+    wk = pk.reshape(nb, Hkv, BS, d)[blk0, :, o]
+    wv = pv.reshape(nb, Hkv, d, BS)[blk0, :, :, o]
+    wk[~ok], wv[~ok] = 0, 0
+    assert np.array_equal(u16(k_out), wk) and np.array_equal(u16(v_out), wv)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Hkv", [1, 3, 8])
+def test_gather_edges(d, Hkv):
+    say(f"[gpu] gather edges d={d} Hkv={Hkv}")
+    _gather_case([0], [1], Hkv, d, 1)
+    _gather_case([7], [1], Hkv, d, 2)
+    for i, (a, n) in enumerate([(0, 32), (1, 31), (8, 33), (15, 64), (16, 65), (5, 96), (31, 7)]):
+        _gather_case([a], [n], Hkv, d, 10 + i)
+    _gather_case([3, 0, 40, 9, 0, 15, 2], [0, 17, 1, 0, 33, 8, 9], Hkv, d, 30)
+    _gather_case(list(range(70)), [1, 2, 3, 5, 7, 9, 0] * 10, Hkv, d, 31, missing=12)
+    _gather_case([-5, 3], [20, 40], Hkv, d, 32)    # a start before the sequence: zero rows
+
+
+def test_gather_large_with_nontemporal_loads():
+    rng = np.random.Generator(np.random.PCG64(5))
+    lens = [int(x) for x in rng.integers(900, 1200, size=17)]
+    starts = [int(x) for x in rng.integers(0, 50, size=17)]
+    assert sum(lens) * 8 * 128 * 4 > 64 << 20
+    say(f"[gpu] gather large: {sum(lens)} tokens")
+    _gather_case(starts, lens, 8, 128, 6, missing=3)
