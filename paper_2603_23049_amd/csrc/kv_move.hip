@@ -5,6 +5,8 @@
 // layout allows, and every block id or slot read from device memory is
 // range-checked in the kernel before use, so a bad table entry skips its row
 // rather than touching memory outside the pool.
+#include <type_traits>
+
 #include "pcr_internal.h"
 
 namespace pcr {
@@ -16,9 +18,11 @@ typedef unsigned short u16;
 // Output rows per gather workgroup: 16 and 64 were 2-5% slower on 268 MB, 16 20% on two
 // kv heads.
 constexpr int kGatherTile = 32;
-// Output bytes from which the gather reads K with non-temporal loads: what a call this
-// large reads is not in the caches, and passing them by saved 3-15% of a gather of
-// 163-268 MB; below, it cost 5-10% on data that still was (10-30 MB).
+// Input bytes from which append and gather read with non-temporal loads: what a call
+// this large reads has left the caches (32 MB of L2; the 256 MB behind it hold the
+// writes too), and passing them by saved 11% of a 151 MB ragged append (35.8 -> 31.9 us)
+// and 3-15% of a gather of 163-268 MB. Below it inputs of a producer kernel are still
+// cached, and non-temporal loads cost 12-20% (appends of 14-33 MB).
 constexpr int64_t kNtBytes = 64ll << 20;
 // New tokens per append workgroup: 32 measured as fast as 16 on block-aligned slot lists
 // and 31% faster on the RAG mix's (whose tiles start inside chunks); 64 was 3.5% slower
@@ -26,33 +30,51 @@ constexpr int64_t kNtBytes = 64ll << 20;
 constexpr int kAppendTile = 32;
 
 // ---------------------------------------------------------------------------
-// append: grid (ceil(T/TILE), Hkv), 256 threads. One workgroup writes TILE new
+// append: grid (ceil(T/TILE), Hkv), 256 threads. One workgroup writes about TILE new
 // tokens of one kv head. K rows are copied 16 B at a time. V is written d-major
 // inside each block: the tile's V rows go through LDS, and each aligned run of 8
 // slots of one dim (a 16-byte chunk of a block's V) that the tile's tokens fill is
 // written by one 16-byte store. A chunk the tile fills only in part (a run of
-// slots that starts or ends inside it: a sequence boundary, a tile edge, a slot
-// list that is not 8-aligned) gets element stores for its filled slots.
+// slots that starts or ends inside it) gets element stores for its filled slots.
+// Tokens that go on inside the pool block of the token before the tile belong to the
+// tile before, so a tile leaves out up to 15 tokens at its start and takes up to 15
+// after its end: no block is written by two workgroups, whose XCDs' L2s would each write
+// parts of its lines, and chunks are cut only where a sequence starts or ends in them.
+// (18480 tokens of 60 ragged sequences, 151 MB: 39.2 us with tiles cut at token 32,
+// 35.8 with whole blocks, 31.9 = 4.7 TB/s with the non-temporal loads; 32 x 1024 aligned
+// tokens, 268 MB, 56 us = 4.8 TB/s either way. A 256 MB device copy runs at 5.4.)
+// NT: the input rows are read with non-temporal loads. (The pool is written with
+// ordinary stores, which merge a block's 16-byte chunks into lines in the L2:
+// non-temporal ones took 1.5 to 2 times as long.)
 // ---------------------------------------------------------------------------
-template <int D, int TILE>
+template <int D, int TILE, bool NT>
 __global__ __launch_bounds__(256) void append_kv_kernel(
     u16 *__restrict__ pool_k, u16 *__restrict__ pool_v, int32_t num_blocks, int32_t Hkv,
     const u16 *__restrict__ k_new, const u16 *__restrict__ v_new,
     const int32_t *__restrict__ slot_mapping, int32_t T)
 {
-    static_assert(TILE <= 64, "one wave ranks the chunk runs");
+    constexpr int EXT = kBlockSize - 1;        // tokens after the tile it may take
+    constexpr int ROWS = TILE + EXT;
+    static_assert(ROWS < 64, "one wave ranks the chunk runs");
+    static_assert(TILE >= kBlockSize, "a tile starts a block");
     constexpr int CPR = D / 8;                 // 16-B chunks per row
     constexpr int NCH = (TILE * CPR + 255) / 256;
-    __shared__ u16 vs[TILE][D + 8];            // +8 elements: stagger rows across banks
-    __shared__ int32_t slots[TILE];
-    __shared__ int32_t runs[TILE];             // (first token << 8) | tokens, one per chunk run
-    __shared__ int32_t n_runs;
+    static_assert(EXT * CPR <= 256, "one chunk of the rows after the tile per thread");
+    __shared__ __attribute__((aligned(16))) u16 vs[ROWS][D + 8];   // +8 elements: stagger rows across banks
+    __shared__ int32_t slots[ROWS];            // -1: no slot, or another tile's
+    __shared__ int32_t runs[ROWS];             // (first token << 8) | tokens, one per chunk run
+    __shared__ int32_t n_runs, n_rows;
 
     const int tile = blockIdx.x, g = blockIdx.y, tid = threadIdx.x;
     const int tok0 = tile * TILE;
 
-    // The K/V rows do not depend on the slot list: their loads go out first, so the two
-    // memory round trips (slots, rows) overlap.
+    auto load = [&](const u16 *src) __attribute__((always_inline)) -> u32x4 {
+        auto *p = reinterpret_cast<const u32x4 *>(src);
+        if constexpr (NT) return __builtin_nontemporal_load(p);
+        return *p;
+    };
+    // The tile's K/V rows do not depend on the slot list: their loads go out first, so the
+    // two memory round trips (slots, rows) overlap.
     u32x4 kv[NCH], vv[NCH];
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
@@ -61,52 +83,73 @@ __global__ __launch_bounds__(256) void append_kv_kernel(
         vv[i] = u32x4{0u, 0u, 0u, 0u};
         if (c < TILE * CPR && tok0 + r < T) {
             const int64_t src = ((int64_t)(tok0 + r) * Hkv + g) * D + cc * 8;
-            kv[i] = *reinterpret_cast<const u32x4 *>(k_new + src);
-            vv[i] = *reinterpret_cast<const u32x4 *>(v_new + src);
+            kv[i] = load(k_new + src);
+            vv[i] = load(v_new + src);
         }
     }
-    if (tid < TILE) {
-        const int t = tok0 + tid;
+    if (tid < 64) {                            // wave 0: the slots, and the chunk runs
+        // Lane 63 reads the slot of the token before the tile (all slots in one load).
+        const int t = tid == 63 ? tok0 - 1 : tok0 + tid;
         int32_t sl = -1;
-        if (t < T) {
+        if ((tid < ROWS || tid == 63) && t >= 0 && t < T) {
             sl = slot_mapping[t];
             if (sl < 0 || sl / kBlockSize >= num_blocks) sl = -1;
         }
-        slots[tid] = sl;
-    }
-    __syncthreads();
-
-#pragma unroll
-    for (int i = 0; i < NCH; ++i) {
-        const int c = tid + 256 * i, r = c / CPR, cc = c % CPR;
-        if (c < TILE * CPR && tok0 + r < T) {
-            *reinterpret_cast<u32x4 *>(&vs[r][cc * 8]) = vv[i];
-            const int32_t sl = slots[r];
-            if (sl >= 0) {
-                const int64_t blk = sl / kBlockSize, o = sl % kBlockSize;
-                const int64_t dst = ((blk * Hkv + g) * kBlockSize + o) * D + cc * 8;
-                *reinterpret_cast<u32x4 *>(pool_k + dst) = kv[i];
-            }
-        }
-    }
-    // Chunk runs (wave 0): a token starts one when its slot is valid and either opens an
-    // aligned chunk of 8 slots or does not follow the previous token's slot; the run
-    // goes on over the following tokens until the next start or invalid slot (a
-    // continuing token's slot is its predecessor's plus one, inside the same chunk).
-    if (tid < 64) {
-        const int32_t sl = tid < TILE ? slots[tid] : -1;
+        // the slot of the token before this one (the wave rotated by one lane: DPP wave_ror:1)
+        const int32_t before = __builtin_amdgcn_update_dpp(sl, sl, 0x13C, 0xf, 0xf, false);
+        if (tid == 63) sl = -1;
+        const bool follows = sl >= 0 && before >= 0 && sl == before + 1;
+        // heads: tokens that do not go on inside the block of the token before them. The
+        // tile's own tokens run from its first head to the first head at or after its end
+        // (both within 15 tokens: a block has 16 slots).
+        const uint64_t heads = ~__builtin_amdgcn_ballot_w64(follows && sl % kBlockSize != 0);
+        const uint64_t rest = heads >> TILE;
+        const int first = (int)__builtin_ctzll(heads);
+        const int last = rest ? min(ROWS, TILE + (int)__builtin_ctzll(rest)) : ROWS;
+        if (tid < first || tid >= last) sl = -1;
+        // A token starts a chunk run when its slot is valid and either opens an aligned chunk
+        // of 8 slots or does not follow the previous token's slot; the run goes on over the
+        // following tokens until the next start or invalid slot (a continuing token's slot
+        // is its predecessor's plus one, inside the same chunk).
         const bool valid = sl >= 0;
-        const bool start = valid && (tid == 0 || sl % 8 == 0 || slots[tid - 1] != sl - 1);
+        const bool start = valid && (tid == 0 || sl % 8 == 0 || !follows);
         const uint64_t starts = __builtin_amdgcn_ballot_w64(start);
-        const uint64_t stops = starts | ~__builtin_amdgcn_ballot_w64(valid);   // bits past TILE are stops
+        const uint64_t stops = starts | ~__builtin_amdgcn_ballot_w64(valid);   // bits past ROWS are stops
         if (start) {
             const uint64_t after = tid == 63 ? 0ull : stops >> (tid + 1);
             const int len = after ? 1 + __builtin_ctzll(after) : 64 - tid;
             const int idx = __builtin_popcountll(starts & ((1ull << tid) - 1ull));
             runs[idx] = (tid << 8) | len;
         }
-        if (tid == 0) n_runs = __builtin_popcountll(starts);
+        if (tid == 0) {
+            n_runs = __builtin_popcountll(starts);
+            n_rows = last;
+        }
+        if (tid < ROWS) slots[tid] = sl;
     }
+    __syncthreads();
+
+    auto put_row = [&](int r, int cc, u32x4 kw, u32x4 vw) __attribute__((always_inline)) {
+        const int32_t sl = slots[r];
+        if (sl < 0) return;
+        *reinterpret_cast<u32x4 *>(&vs[r][cc * 8]) = vw;
+        const int64_t blk = sl / kBlockSize, o = sl % kBlockSize;
+        *reinterpret_cast<u32x4 *>(pool_k + ((blk * Hkv + g) * kBlockSize + o) * D + cc * 8) = kw;
+    };
+    u32x4 ke = {0u, 0u, 0u, 0u}, ve = {0u, 0u, 0u, 0u};
+    const int re = TILE + tid / CPR, ce = tid % CPR;   // this thread's chunk of the rows after the tile
+    const bool ext = re < n_rows;
+    if (ext) {
+        const int64_t src = ((int64_t)(tok0 + re) * Hkv + g) * D + ce * 8;
+        ke = load(k_new + src);
+        ve = load(v_new + src);
+    }
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) {
+        const int c = tid + 256 * i;
+        if (c < TILE * CPR) put_row(c / CPR, c % CPR, kv[i], vv[i]);
+    }
+    if (ext) put_row(re, ce, ke, ve);
     __syncthreads();
 
     // V: task = (run, dim)
@@ -306,12 +349,19 @@ hipError_t launch_append_kv(const pcr_kv_pool &pool, const void *k_new, const vo
     auto *pv = static_cast<u16 *>(pool.v);
     auto *kn = static_cast<const u16 *>(k_new);
     auto *vn = static_cast<const u16 *>(v_new);
-    if (pool.head_dim == 128)
-        hipLaunchKernelGGL((append_kv_kernel<128, kAppendTile>), grid, dim3(256), 0, s, pk, pv, pool.num_blocks,
-                           pool.num_kv_heads, kn, vn, slot_mapping, T);
-    else
-        hipLaunchKernelGGL((append_kv_kernel<64, kAppendTile>), grid, dim3(256), 0, s, pk, pv, pool.num_blocks,
-                           pool.num_kv_heads, kn, vn, slot_mapping, T);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, pk, pv, pool.num_blocks, pool.num_kv_heads, kn, vn,
+                           slot_mapping, T);
+    };
+    const int64_t in_bytes = 2 * (int64_t)T * pool.num_kv_heads * pool.head_dim * 2;
+    const bool nt = in_bytes >= kNtBytes;
+    if (pool.head_dim == 128) {
+        if (nt) launch(append_kv_kernel<128, kAppendTile, true>);
+        else launch(append_kv_kernel<128, kAppendTile, false>);
+    } else {
+        if (nt) launch(append_kv_kernel<64, kAppendTile, true>);
+        else launch(append_kv_kernel<64, kAppendTile, false>);
+    }
     return hipGetLastError();
 }
 

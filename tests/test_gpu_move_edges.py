@@ -1,4 +1,4 @@
-"""GPU: gather against plain numpy indexing, bit for bit, where its tiles of 32 rows and
+"""GPU: gather and append against plain numpy indexing, bit for bit, where their tiles of 32 tokens and
 chunks of 8 slots can go wrong: ranges that start and end inside chunks and blocks, empty
 and one-token sequences, rows whose block is missing, sizes on both sides of the
 non-temporal loads."""
@@ -72,3 +72,58 @@ def test_gather_large_with_nontemporal_loads():
     assert sum(lens) * 8 * 128 * 4 > 64 << 20
     say(f"[gpu] gather large: {sum(lens)} tokens")
     _gather_case(starts, lens, 8, 128, 6, missing=3)
+
+
+def _append_case(slots, nb, Hkv, d, seed):
+    rng = np.random.Generator(np.random.PCG64(seed))
+    T = len(slots)
+    slots = np.asarray(slots, np.int32)
+    pk, pv = _pool(rng, nb, Hkv, d)
+    k_new, v_new = synth.normal_bf16(rng, (T, Hkv, d)), synth.normal_bf16(rng, (T, Hkv, d))
+    pool = pcr.KVPool(dev(pk), dev(pv), Hkv, d)
+    pcr.append_kv(pool, dev(k_new), dev(v_new), dev(slots))
+    torch.cuda.synchronize()
+    ok = (slots >= 0) & (slots // BS < nb)
+    sl = slots[ok].astype(np.int64)
+    pk.reshape(nb, Hkv, BS, d)[sl // BS, :, sl % BS] = k_new[ok]
+    pv.reshape(nb, Hkv, d, BS)[sl // BS, :, :, sl % BS] = v_new[ok]
+    assert np.array_equal(u16(pool.k), pk), "K pool"
+    assert np.array_equal(u16(pool.v), pv), "V pool"
+
+
+def _segments(rng, n, nb):
+    """A slot list of n runs of consecutive slots, each from anywhere in blocks of its own."""
+    blocks = iter(rng.permutation(nb // 4) * 4)
+    out = []
+    for _ in range(n):
+        base = int(next(blocks)) * BS + int(rng.integers(0, BS))
+        out += range(base, base + int(rng.integers(1, 48)))
+    return out
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Hkv", [1, 3, 8])
+def test_append_edges(d, Hkv):
+    """Runs that cross tile edges (multiples of 32 tokens) inside blocks and chunks, at
+    every offset; slots that are skipped in the middle of a run; runs in falling order."""
+    say(f"[gpu] append edges d={d} Hkv={Hkv}")
+    rng = np.random.Generator(np.random.PCG64(d + Hkv))
+    for T in (1, 15, 16, 31, 32, 33, 47, 48, 49, 64, 100):
+        for first in (0, 1, 7, 8, 15):
+            _append_case(range(first, first + T), 8, Hkv, d, 100 + T + first)
+    seg = _segments(rng, 40, 400)
+    _append_case(seg, 400, Hkv, d, 7)
+    holes = np.asarray(seg)
+    holes[rng.integers(0, len(seg), size=60)] = rng.choice([-1, 400 * BS, 2**31 - 1], size=60)
+    _append_case(holes, 400, Hkv, d, 8)
+    _append_case(seg[::-1], 400, Hkv, d, 9)
+    _append_case(rng.permutation(400 * BS)[:777], 400, Hkv, d, 10)
+
+
+def test_append_large_ragged_with_nontemporal_loads():
+    rng = np.random.Generator(np.random.PCG64(11))
+    nb = 4 * 800
+    seg = _segments(rng, 790, nb)
+    assert len(seg) * 8 * 128 * 4 > 64 << 20
+    say(f"[gpu] append large ragged: {len(seg)} tokens")
+    _append_case(seg, nb, 8, 128, 12)
