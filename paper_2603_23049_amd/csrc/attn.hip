@@ -363,6 +363,40 @@ __device__ __forceinline__ Item locate_item(const AttnWorkMap &wm, int32_t Hkv)
     return it;
 }
 
+// Output of one wave's 32 rows x W dims through LDS, so that whole lines leave it 16
+// bytes a lane. In the accumulator layout a lane holds 4 consecutive dims of its row at
+// a time: stored directly (8 bytes a lane, 32 rows in one instruction) the rows' lines
+// went out in 32-byte pieces, and a workgroup's end waited for them: 4.9 us from one
+// workgroup's last store to the next one's start on its compute unit, 1.3 us with
+// whole lines (256 rows x 128 dims; the turnover itself is 0.25 us).
+// Rows of W bf16 lie back to back in the wave's own LDS area; 16-byte chunk c of row q is
+// at chunk c ^ (q % (W/8)), and its two 8-byte halves change places in rows 16.., so that
+// neither the 8-byte writes nor the 16-byte reads meet in a bank.
+template <int W>
+__device__ __forceinline__ void stage_row(char *stage, int lane, int chunk, f32x4 v)
+{
+    const int q = lane & 31, half = lane >> 5;
+    const bf16x4 bv = __builtin_convertvector(v, bf16x4);   // dims 8 chunk + 4 half ..
+    *reinterpret_cast<u32x2 *>(stage + q * (W * 2) + ((chunk ^ (q % (W / 8))) * 16) + ((half ^ (q >> 4)) * 8)) =
+        __builtin_bit_cast(u32x2, bv);
+}
+
+// orow: the output row of lane q's row (-1: none); the W dims go to column col of rows of D.
+template <int W, int D = W>
+__device__ __forceinline__ void store_rows(const char *stage, int lane, int orow, u16 *__restrict__ out, int col)
+{
+    constexpr int CH = W / 8;             // chunks per row
+    asm volatile("" ::: "memory");        // after the wave's stage_row writes (LDS runs them in order)
+#pragma unroll
+    for (int i = 0; i < 32 * CH / 64; ++i) {
+        const int id = i * 64 + lane, q = id / CH, c = id % CH;
+        const int row = __shfl(orow, q);
+        u32x4 v = *reinterpret_cast<const u32x4 *>(stage + q * (W * 2) + ((c ^ (q % CH)) * 16));
+        if (q >> 4) v = u32x4{v[2], v[3], v[0], v[1]};
+        if (row >= 0) *reinterpret_cast<u32x4 *>(out + (int64_t)row * D + col + c * 8) = v;
+    }
+}
+
 template <int D, int MODE>
 __global__ __launch_bounds__(kThreads) void prefill_attn_kernel(
     const u16 *__restrict__ q, const u16 *__restrict__ pool_k, const u16 *__restrict__ pool_v,
@@ -864,23 +898,23 @@ __global__ __launch_bounds__(kThreads) void prefill_attn_kernel(
     }
     while (ph < phases) phase_end();
 
+    // This lane's output row, -1 for a row past the end (T * Hq fits 31 bits).
+    const int orow = row_valid && tq < T ? (int)(tq * Hq) + h : -1;
     if constexpr (ROWS) {
         // ---- row halves: every group saw all keys of its rows; normalise, store ----
+        // (the last phase's barrier is behind every read of the tile buffers)
         const float inv = 1.f / (l_run + ((lane & 16) ? tsum[1] : tsum[0]));
-        if (row_valid && tq < T) {
-            u16 *orow = out + (tq * Hq + h) * D;
+        char *stage = &lds[0][0] + wave * (32 * D * 2);
 #pragma unroll
-            for (int k = 0; k < MT; ++k)
+        for (int k = 0; k < MT; ++k)
 #pragma unroll
-                for (int r4 = 0; r4 < 4; ++r4) {
-                    f32x4 v;
+            for (int r4 = 0; r4 < 4; ++r4) {
+                f32x4 v;
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) v[c] = o_acc[k][4 * r4 + c] * inv;
-                    const bf16x4 bv = __builtin_convertvector(v, bf16x4);
-                    const int d0 = 32 * k + 8 * r4 + 4 * half;
-                    *reinterpret_cast<u32x2 *>(orow + d0) = __builtin_bit_cast(u32x2, bv);
-                }
-        }
+                for (int c = 0; c < 4; ++c) v[c] = o_acc[k][4 * r4 + c] * inv;
+                stage_row<D>(stage, lane, 4 * k + r4, v);
+            }
+        store_rows<D>(stage, lane, orow, out, 0);
         return;
     }
 
@@ -942,21 +976,19 @@ __global__ __launch_bounds__(kThreads) void prefill_attn_kernel(
         }
     }
     const float inv = 1.f / (a0 * l_tot + a1 * l1);
-    if (row_valid && tq < T) {
-        u16 *orow = out + (tq * Hq + h) * D;
+    char *stage = &lds[0][0] + 2 * kGroupWaves * XW * 64 * 16 + wave * (32 * MH * 32 * 2);
+    static_assert(2 * kGroupWaves * (XW * 64 * 16 + 32 * MH * 32 * 2) <= (int)sizeof(lds), "merge and output area");
 #pragma unroll
-        for (int k = 0; k < MH; ++k)
+    for (int k = 0; k < MH; ++k)
 #pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) {
-                const f32x4 o1 = xi[(k * 4 + r4) * 64 + lane];
-                f32x4 v;
+        for (int r4 = 0; r4 < 4; ++r4) {
+            const f32x4 o1 = xi[(k * 4 + r4) * 64 + lane];
+            f32x4 v;
 #pragma unroll
-                for (int c = 0; c < 4; ++c) v[c] = (a0 * o_acc[my0 + k][4 * r4 + c] + a1 * o1[c]) * inv;
-                const bf16x4 bv = __builtin_convertvector(v, bf16x4);
-                const int d0 = 32 * (my0 + k) + 8 * r4 + 4 * half;
-                *reinterpret_cast<u32x2 *>(orow + d0) = __builtin_bit_cast(u32x2, bv);
-            }
-    }
+            for (int c = 0; c < 4; ++c) v[c] = (a0 * o_acc[my0 + k][4 * r4 + c] + a1 * o1[c]) * inv;
+            stage_row<MH * 32>(stage, lane, 4 * k + r4, v);
+        }
+    store_rows<MH * 32, D>(stage, lane, orow, out, my0 * 32);
 }
 
 // One wave: takes a free slot for the launch with this output (none free: the launch
