@@ -159,6 +159,12 @@ __device__ __forceinline__ void dma16(const char *base, uint32_t lane_off, uint3
                  "s"(reinterpret_cast<const char *>(sb)), "s"(m0)
                  : "memory", "m0");
 }
+// The same with a full address per lane.
+__device__ __forceinline__ void dma16_at(const char *src, uint32_t lds_dst)
+{
+    const unsigned m0 = __builtin_amdgcn_readfirstlane(lds_dst);
+    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(m0) : "memory", "m0");
+}
 #pragma clang diagnostic pop
 
 // Wait until at most N vector-memory operations of this wave are outstanding
@@ -469,9 +475,12 @@ __global__ __launch_bounds__(kThreads) void prefill_attn_kernel(
     const bool row_valid = R < rows_total;
     const int Rc = row_valid ? R : rows_total - 1;
     const int i = Rc / G, hl = Rc - i * G;
-    const int h = g * G + hl;
     const int limit = p + i;                         // last key this row attends to
-    const int64_t tq = (int64_t)t0 + i;
+    const int tq = min(t0 + i, T - 1);               // (T * Hq fits 31 bits)
+    const int qrow = tq * Hq + g * G + hl;           // its row of q and out
+    // Its output row, -1 past the end; held in one register over the loop.
+    int orow = row_valid ? qrow : -1;
+    asm volatile("" : "+v"(orow));
 
     const int wg_last = min(rows_total - 1, row0 + RPW - 1);
     const int all_tiles = key_tiles(p + wg_last / G);
@@ -494,18 +503,7 @@ __global__ __launch_bounds__(kThreads) void prefill_attn_kernel(
     const int w_min_limit = p + w_first / G;
     const int valid_blocks = min((total + kBlockSize - 1) / kBlockSize, max_blocks);
 
-    // Q^T operand fragments (k-step ks: dims 16ks + 8half .. +7 of this lane's row). The
-    // loads go out here; the scaling waits until the first K tile has been requested.
-    // All eight loads are unconditional, so that they are in flight together (a row past
-    // the end reads row 0 of head 0, which exists since T > 0, and is zeroed later).
-    const bool q_ok = tq < T;
-    u32x4 q_raw[KSTEPS];
-    bf16x8 qf[KSTEPS];    // the Q^T operand, set once K(0) has been requested
-    {
-        const u16 *qrow = q + (q_ok ? (tq * Hq + h) * D : 0);
-#pragma unroll
-        for (int ks = 0; ks < KSTEPS; ++ks) q_raw[ks] = *reinterpret_cast<const u32x4 *>(qrow + 16 * ks + 8 * half);
-    }
+    bf16x8 qf[KSTEPS];    // the Q^T operand (k-step ks: dims 16ks + 8half .. +7 of this lane's row)
 
     f32x16 o_acc[MT];
 #pragma unroll
@@ -808,16 +806,44 @@ __global__ __launch_bounds__(kThreads) void prefill_attn_kernel(
     // already run near its bandwidth.
     const bool loader = !ROWS || grp == 0;
     int64_t ids_v[kTileBlocks], ids_k[kTileBlocks];   // payload byte offsets
+    int32_t ids_next[kTileBlocks];
     tile_ids(0, ids_raw);
+    tile_ids(1, ids_next);
     to_offs(ids_raw, ids_v);
     if (n > 0 && loader) issue_k(0, ids_v);            // K(0) for C(-1)
-    tile_ids(1, ids_raw);
-    to_offs(ids_raw, ids_k);
-    // Q^T operand fragments (k-step ks: dims 16ks + 8half .. +7 of this lane's row),
-    // the bf16 input as it is.
+    // Q^T operand fragments (k-step ks: dims 16ks + 8half .. +7 of this lane's row), the
+    // bf16 input as it is, requested after K(0): eight loads in the operand layout touch 32
+    // rows for 32 bytes each, and K(0) waited behind them (8B layer: 1.2 us from the item's
+    // lookup to K(0)'s request, 0.6 us now). Key halves take whole rows through LDS, each
+    // wave's 32 rows by direct loads into this group's V buffers, free until after the
+    // barrier below, swizzled as a K tile (8B layer 65.1 -> 64.5 us with both changes; row
+    // halves read the operand layout, as the way through LDS cost them 6 spilled registers
+    // and the 70B layer 1%).
+    if constexpr (ROWS) {
 #pragma unroll
-    for (int ks = 0; ks < KSTEPS; ++ks) qf[ks] = as_bf16x8(q_ok ? q_raw[ks] : u32x4{0u, 0u, 0u, 0u});
-    wait_vmem();
+        for (int ks = 0; ks < KSTEPS; ++ks)
+            qf[ks] = *reinterpret_cast<const bf16x8 *>(q + (int64_t)qrow * D + 16 * ks + 8 * half);
+        to_offs(ids_next, ids_k);
+        wait_vmem();
+    } else {
+        constexpr int kQBytes = kRowsPerWave * D * 2;
+        static_assert(kGroupWaves * kQBytes <= 2 * Geo::VBYTES, "Q in the V buffers");
+        const uint32_t q_off = (uint32_t)(2 * Geo::KBYTES + wg * kQBytes);
+#pragma unroll
+        for (int u = 0; u < kQBytes / 1024; ++u) {
+            const int id = u * 64 + lane, r = id / CPR, pc = id % CPR;
+            const int64_t row = __shfl(qrow, r);
+            dma16_at(reinterpret_cast<const char *>(q + row * D) + ((pc ^ (r % CPR)) * 16), lds_addr + q_off + u * 1024);
+        }
+        to_offs(ids_next, ids_k);
+        wait_vmem();
+        const char *q_tile = &lds[lgrp][0] + q_off;
+#pragma unroll
+        for (int ks = 0; ks < KSTEPS; ++ks)
+            qf[ks] = *reinterpret_cast<const bf16x8 *>(q_tile + qc * (2 * D) + (((2 * ks + half) ^ (qc % CPR)) * 16));
+        // read before another wave of the group loads V(0) over it
+        __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+    }
     __syncthreads();
 
     const int n0 = split, n1 = ROWS ? ntiles : ntiles - split;
@@ -898,8 +924,6 @@ __global__ __launch_bounds__(kThreads) void prefill_attn_kernel(
     }
     while (ph < phases) phase_end();
 
-    // This lane's output row, -1 for a row past the end (T * Hq fits 31 bits).
-    const int orow = row_valid && tq < T ? (int)(tq * Hq) + h : -1;
     if constexpr (ROWS) {
         // ---- row halves: every group saw all keys of its rows; normalise, store ----
         // (the last phase's barrier is behind every read of the tile buffers)
@@ -955,7 +979,7 @@ __global__ __launch_bounds__(kThreads) void prefill_attn_kernel(
     if constexpr (MODE == kKeySplit) {
         if (part >= 0) {
             // A chunk's partial result, in the lane layout (1 KB per wave-wide store).
-            if (row_valid && tq < T) {
+            if (orow >= 0) {
                 f32x4 *po = reinterpret_cast<f32x4 *>(&split_o[0][0][0] + (int64_t)part * kSplitPartO) +
                             wg * MT * 4 * 64 + lane;
                 f32x2 *pml = reinterpret_cast<f32x2 *>(&split_ml[0][0][0] + (int64_t)part * kSplitPartML) +
