@@ -7,12 +7,14 @@ built, or the library reports an error, these functions raise.
 from __future__ import annotations
 
 import ctypes
+import math
 import os
 from dataclasses import dataclass
 from typing import Optional, Sequence
 
 import numpy as np
 
+_INT32 = np.dtype(np.int32)
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libpcr.so")
 
@@ -152,13 +154,21 @@ def _ptr(x) -> Optional[int]:
     if x is None:
         return None
     if isinstance(x, np.ndarray):
-        return x.ctypes.data
+        try:        # 0.3 us against 1.1 us for x.ctypes; writable, contiguous, not empty
+            return ctypes.addressof(ctypes.c_char.from_buffer(x))
+        except (TypeError, ValueError, BufferError):
+            return x.ctypes.data
     return x.data_ptr()
 
 
 def _stream(stream) -> Optional[int]:
+    """hipStream_t of a stream, the current device's current stream for None. A small call
+    is bound by the host (8-12 us a call against 3-9 us of kernels), and the raw handle
+    costs 0.1 us where torch.cuda.current_stream(), which builds a Stream object, costs 2.5."""
     if stream is None:
         import torch
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
@@ -166,6 +176,8 @@ def _stream(stream) -> Optional[int]:
 
 
 def _i32_host(a) -> np.ndarray:
+    if isinstance(a, np.ndarray) and a.dtype is _INT32 and a.flags.c_contiguous:
+        return a
     return np.ascontiguousarray(np.asarray(a, dtype=np.int32))
 
 
@@ -176,7 +188,7 @@ def _numel(x) -> int:
 def _need(x, n: int, what: str):
     """The library reads device arrays by the lengths it is given, which it cannot check
     against the allocations: refuse, before the call, a tensor shorter than that."""
-    if x is not None and _numel(x) < n:
+    if x is not None and (x.size if isinstance(x, np.ndarray) else x.numel()) < n:
         raise ValueError(f"{what} holds {_numel(x)} elements, the call reads {n}")
 
 
@@ -315,7 +327,7 @@ def prefix_prefill_attn(q, pool: KVPool, block_tables, prefix_lens, cu_suffix, h
     if hcu.shape[0] != B + 1:
         raise ValueError("host_cu_suffix must have B+1 entries")
     if sm_scale is None:
-        sm_scale = 1.0 / float(np.sqrt(pool.head_dim))
+        sm_scale = 1.0 / math.sqrt(pool.head_dim)
     T = int(hcu[-1]) if B > 0 else 0
     _need(q, T * int(num_q_heads) * pool.head_dim, "q")
     _need(out, T * int(num_q_heads) * pool.head_dim, "out")
@@ -362,7 +374,7 @@ def decode_attn(q, pool: KVPool, block_tables, context_lens, host_context_lens, 
     hcl = _i32_host(host_context_lens)
     B = int(hcl.shape[0])
     if sm_scale is None:
-        sm_scale = 1.0 / float(np.sqrt(pool.head_dim))
+        sm_scale = 1.0 / math.sqrt(pool.head_dim)
     _decode_need(q, out, block_tables, context_lens, B, num_q_heads, pool)
     if workspace is None and B > 0:
         import torch
@@ -390,7 +402,7 @@ def decode_attn_noalloc(q, pool: KVPool, block_tables, context_lens, host_contex
     hcl = _i32_host(host_context_lens)
     B = int(hcl.shape[0])
     if sm_scale is None:
-        sm_scale = 1.0 / float(np.sqrt(pool.head_dim))
+        sm_scale = 1.0 / math.sqrt(pool.head_dim)
     _decode_need(q, out, block_tables, context_lens, B, num_q_heads, pool)
     p = pool.c()
     _check(lib().pcr_decode_attn_noalloc(_ptr(q), ctypes.byref(p), _ptr(block_tables), int(block_tables.shape[1]),

@@ -82,3 +82,17 @@ def test_pipeline_refuses_short_layer_tensors_and_batch():
                           np.array([16], np.int32), hcu, Hq, 0.125)
     with pytest.raises(ValueError, match="slot_mapping"):
         short.c()
+
+
+def test_pointers_of_host_arrays():
+    """Whatever the array's form, the address handed to the library is its first element's."""
+    a = np.arange(12, dtype=np.int32)
+    ro = a.copy()
+    ro.flags.writeable = False
+    for x in (a, a[3:], a[::2], a.reshape(3, 4).T, ro, a[:0], np.zeros((), np.int32), a.astype(np.float32)):
+        assert pcr._ptr(x) == x.__array_interface__["data"][0]
+    assert pcr._ptr(None) is None
+    for x in (a[::2], a.astype(np.int64), [1, 2, 3], a.astype(">i4")):
+        y = pcr._i32_host(x)
+        assert y.dtype == np.int32 and y.flags.c_contiguous and y.dtype.isnative and list(y) == list(x)
+    assert pcr._i32_host(a) is a and pcr._i32_host(ro) is ro
