@@ -263,9 +263,9 @@ pcr_status pcr_prefix_prefill_attn(const void *q, const pcr_kv_pool *pool,
  * pcr_prefill_attn_set_schedule -- how pcr_prefix_prefill_attn (and the pipelines'
  * attention) divides a launch among workgroups; a tuning and testing control, not
  * part of the method. Every schedule computes the same result (Sec. 2.2).
- *   PCR_ATTN_SCHEDULE_AUTO (the default): row halves when that still gives at
- *     least two workgroups per compute unit, else key halves, for launches that leave
- *     compute units idle with the keys cut into chunks; pcr_pipeline_run and
+ *   PCR_ATTN_SCHEDULE_AUTO (the default): of the two below the one estimated to take
+ *     less time when there are more workgroups than compute units, else key halves, for
+ *     launches that leave compute units idle with the keys cut into chunks; pcr_pipeline_run and
  *     pcr_pipeline_run_offload, whose pull-kernel loads share the compute units
  *     with the attention, take key halves (shorter workgroups let the copy
  *     workgroups onto a compute unit sooner);

@@ -9,18 +9,17 @@
 // G = Hq/Hkv, are packed token-major (row r = token r/G, head-in-group r%G)
 // so that all rows of a workgroup share one K/V stream. A workgroup has 8 waves in
 // two groups (waves 0-3 and 4-7, 32 rows per wave), so each SIMD runs one wave of
-// each group: one wave's softmax overlaps the other's matrix work. Two schedules:
+// each group: one wave's softmax overlaps the other's matrix work. Three schedules:
 //   key halves: the workgroup takes 128 packed rows; both groups hold the same rows
 //     and walk the two halves of the key range, merged through LDS at the end;
 //   row halves: the workgroup takes 256 packed rows, 128 per group, and both groups
 //     walk the whole key range, group 1 one phase behind, through one copy of each
-//     tile that group 0 loads; no merge.
-// Row halves give each workgroup twice the work for one start-up and no merge; the
-// host takes them when the launch still has at least two workgroups per compute
-// unit, key halves otherwise (twice the workgroups for small launches).
+//     tile that group 0 loads; no merge;
 //   key split: key halves with each row tile's keys cut into chunks, one workgroup each,
 //     whose partial results (O, max, sum) a second kernel merges; for launches that
 //     leave compute units idle.
+// Row halves give each workgroup twice the work for one start-up and no merge; the
+// host takes them when they are estimated to be faster (schedule_time).
 //
 // Per wave and 64-key tile (4 pool blocks), with v_mfma_f32_32x32x16_bf16:
 //   S^T[key][q] = K Q^T   A = K rows from LDS, B = this wave's Q (registers)
@@ -1191,6 +1190,45 @@ int32_t split_chunk(const int32_t *seq, int n, const int32_t *host_prefix_lens, 
     return hi;
 }
 
+// Estimated time in us of a launch on row tiles of rpw rows (128: key halves, 256: row
+// halves): an item takes its fixed part plus its key tiles, whole rounds of n_cu items take
+// the mean item each, and a last round of few items runs faster, at the clock that the
+// idle compute units' power allows (42% of a full round's time and 57% in proportion to
+// its items). Measured with 128 dims (64 dims): 0.84 (0.57) us a key tile and 7 us with key
+// halves, 1.58 (1.2) and 8 with row halves, where one copy of a tile serves twice the
+// rows; 0.7 (0.35) us per 64 keys and 5 for a decode row. The estimates were within 8% of
+// 40 measured launches of 1 to 4 rounds, apart from short ones without a prefix.
+double schedule_time(const int32_t *seq, int n, const int32_t *host_prefix_lens, const int32_t *host_cu_suffix, int G,
+                     int Hkv, int D, int rpw, int n_cu)
+{
+    const bool rows = rpw > kRowsPerWG;
+    const double fixed = rows ? 8.0 : 7.0, dec_tile = 0.7 * D / 128;
+    const double tile = D == 128 ? (rows ? 1.58 : 0.84) : (rows ? 1.2 : 0.57);
+    double total = 0.0, longest = 0.0;
+    int64_t items = 0;
+    for (int k = 0; k < n; ++k) {
+        const int32_t b = seq[k], p = host_prefix_lens[b], sb = host_cu_suffix[b + 1] - host_cu_suffix[b];
+        const int last = key_tiles(p + sb - 1);
+        if (sb == 1 && G <= decode_wave::kMaxCols) {
+            const double t = 5.0 + dec_tile * last;
+            total += t;
+            longest = std::max(longest, t);
+            ++items;
+        } else {
+            const int64_t r = (int64_t)sb * G, nt = (r + rpw - 1) / rpw;
+            const int first = key_tiles(p + (int)((std::min<int64_t>(r, rpw) - 1) / G));
+            total += nt * (fixed + tile * 0.5 * (first + last));
+            longest = std::max(longest, fixed + tile * last);
+            items += nt;
+        }
+    }
+    const double mean = total / items;
+    items *= Hkv;
+    const int64_t rounds = items / n_cu, over = items % n_cu;
+    const double part = 0.42 + 0.57 * over / n_cu;
+    return std::max(rounds * mean + (over ? part * mean : 0.0), longest * (rounds ? 1.0 : part));
+}
+
 // One launch over the sequences seq[0..n) (each with new tokens, n <= kMaxMapSeqs,
 // longest context first): builds the work map, picks the schedule, launches.
 hipError_t launch_group(const int32_t *seq, int n, const u16 *qq, const pcr_kv_pool &pool,
@@ -1200,16 +1238,26 @@ hipError_t launch_group(const int32_t *seq, int n, const u16 *qq, const pcr_kv_p
 {
     const int Hkv = pool.num_kv_heads, G = num_q_heads / Hkv;
     auto rows_of = [&](int32_t b) { return ((int64_t)host_cu_suffix[b + 1] - host_cu_suffix[b]) * G; };
-    int64_t tiles_rows = 0;   // row tiles of 256 rows over the group's sequences, one kv head
-    for (int k = 0; k < n; ++k) tiles_rows += (rows_of(seq[k]) + 2 * kRowsPerWG - 1) / (2 * kRowsPerWG);
-    // Row halves when the launch keeps at least two workgroups per compute unit
-    // with them (each workgroup then pays its start-up and end for twice the work),
-    // unless the caller prefers key halves (shorter workgroups free a compute unit
-    // sooner for copy kernels that share the device).
     int sched = g_schedule.load(std::memory_order_relaxed);
     if (sched == PCR_ATTN_SCHEDULE_AUTO) sched = auto_schedule;
-    const bool rows = sched == PCR_ATTN_SCHEDULE_ROW_HALVES ||
-                      (sched == PCR_ATTN_SCHEDULE_AUTO && tiles_rows * Hkv >= 2 * (int64_t)n_cu);
+    // More key-halves items than compute units: row halves when they are estimated to take
+    // less time (unless the caller prefers key halves, whose shorter workgroups free a
+    // compute unit sooner for copy kernels that share the device). Row halves win where
+    // both fill whole rounds; they lose where their fewer items leave more of the last
+    // round idle, and where the suffixes are shorter than their tiles. Against taking them
+    // from two items per compute unit on (32 query / 8 kv heads of 128): 64 sequences of 32
+    // new tokens on 3000 cached 200 -> 154 us (key halves), 16 of 128 on 4096 142 -> 129 (row
+    // halves), one of 1280 on 8192 199 -> 180 and of 3584 on 8192 505 -> 473 (row halves);
+    // of 40 other shapes none lost 2%.
+    bool rows = sched == PCR_ATTN_SCHEDULE_ROW_HALVES;
+    if (sched == PCR_ATTN_SCHEDULE_AUTO) {
+        int64_t tiles = 0;   // row tiles of 128 rows, one kv head
+        for (int k = 0; k < n; ++k) tiles += (rows_of(seq[k]) + kRowsPerWG - 1) / kRowsPerWG;
+        auto time_of = [&](int rows_per_item) {
+            return schedule_time(seq, n, host_prefix_lens, host_cu_suffix, G, Hkv, pool.head_dim, rows_per_item, n_cu);
+        };
+        rows = tiles * Hkv > n_cu && time_of(2 * kRowsPerWG) < time_of(kRowsPerWG);
+    }
     const int64_t rpw = rows ? 2 * kRowsPerWG : kRowsPerWG;
     // Key tiles per item, 0: no key split.
     const int32_t chunk =

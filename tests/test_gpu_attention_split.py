@@ -134,3 +134,25 @@ def test_output_in_place_of_the_queries_is_not_split():
     pcr.prefix_prefill_attn(q, L.pool, L.bt, L.pl, L.cu, L.pl_np, L.cu_np, L.batch.num_q_heads, q, sm_scale=L.sm_scale)
     torch.cuda.synchronize()
     assert torch.equal(q.view(torch.int16), whole)
+
+
+@pytest.mark.parametrize("pl,sl,G,Hkv,d", [
+    ([300] * 64, [20] * 64, 4, 8, 128),            # suffixes shorter than a tile: key halves
+    ([700], [1280], 4, 8, 128), ([40] * 5, [700] * 5, 4, 8, 64),
+    ([1000], [3600], 2, 8, 128), ([0, 5, 900], [1700, 1, 900], 7, 4, 128),
+])
+def test_default_schedule_of_one_to_four_rounds(pl, sl, G, Hkv, d):
+    """More items than compute units: the default takes one of the two schedules, whole."""
+    say(f"[gpu] default schedule B={len(pl)} s={sl[0]} G={G} Hkv={Hkv} d={d}")
+    L, rows, want = _layer(pl, sl, G, Hkv, d, seed=500 + len(pl) + G)
+    L.attn()
+    torch.cuda.synchronize()
+    _check(L, rows, want, "default")
+    got = L.out.clone()
+    same = []
+    for name in ("key_halves", "row_halves"):
+        with attn_schedule(name):
+            L.attn()
+        torch.cuda.synchronize()
+        same.append(torch.equal(L.out, got))
+    assert any(same)
