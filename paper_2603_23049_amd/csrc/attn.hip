@@ -198,20 +198,26 @@ struct AttnWorkMap {
 enum AttnMode { kKeyHalves = 0, kRowHalves = 1, kKeySplit = 2 };
 
 // Scratch of key-split launches: kSplitSlots slots of kSplitParts partial results per
-// device, held until the process ends. A launch owns one slot from its claim kernel to
-// the last workgroup of its combine kernel. The slot's owner word is the launch's output
-// pointer, which names the launch: two launches in flight never write one output, so
-// the workgroups find their slot by looking for it, and nothing about it is fixed on the
-// host (launches on any streams and threads, and replays of captured graphs, claim
-// theirs when they run). With every slot taken a launch runs unsplit.
+// device, held until the process ends. A launch owns one slot from its claim kernel until
+// every workgroup of its combine kernel has counted itself out. The slot's owner word
+// holds the launch's output pointer, which names the launch: two launches in flight never
+// write one output, so the workgroups find their slot by looking for it, and nothing
+// about it is fixed on the host (launches on any streams and threads, and replays of
+// captured graphs, claim theirs when they run). With every slot taken a launch runs
+// unsplit.
 constexpr int kSplitSlots = 8;
 constexpr int kSplitMinChunk = 4;                        // key tiles of an item, at least
 constexpr int kSplitParts = 256;                         // items of one launch, at most
 constexpr int kSplitPartO = kRowsPerWG * 128 * 4;        // bytes: O of 128 rows x 128 dims, fp32
 constexpr int kSplitPartML = kRowsPerWG * 2 * 8;         // bytes: (max, sum) per lane of 4 waves
 struct SplitControl {
-    unsigned long long owner[kSplitSlots];               // output pointer of the owning launch, 0: free
-    unsigned int done[kSplitSlots];                      // combine workgroups that are through
+    // Output pointer of the slot's last launch (48 bits) and, below it, the counts at which
+    // that launch is through (16 bits). A claim exchanges the word as a whole.
+    unsigned long long owner[kSplitSlots];
+    // Combine workgroups that are through, of all launches so far, per XCD. Each count has
+    // a line to itself: 256 workgroups counting at one address took 2-3 us, and the end of
+    // a launch does not wait for a count to come back.
+    unsigned int done[kSplitSlots][kXcds][32];
 };
 __device__ SplitControl split_control;
 __device__ __attribute__((aligned(1024))) char split_o[kSplitSlots][kSplitParts][kSplitPartO];
@@ -224,7 +230,7 @@ __device__ __forceinline__ int split_slot(const u16 *out)
     const unsigned long long own =
         lane < kSplitSlots ? __hip_atomic_load(&split_control.owner[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
                            : 0ull;
-    const uint64_t mine = __builtin_amdgcn_ballot_w64(own == (unsigned long long)(uintptr_t)out);
+    const uint64_t mine = __builtin_amdgcn_ballot_w64(own >> 16 == (unsigned long long)(uintptr_t)out);
     return mine ? (int)__builtin_ctzll(mine) : -1;
 }
 
@@ -1014,17 +1020,33 @@ __global__ __launch_bounds__(kThreads) void prefill_attn_kernel(
     store_rows<MH * 32, D>(stage, lane, orow, out, my0 * 32);
 }
 
-// One wave: takes a free slot for the launch with this output (none free: the launch
-// finds no slot and runs unsplit).
-__global__ __launch_bounds__(64) void split_claim_kernel(u16 *out)
+// One wave: takes a free slot for the launch with this output and per_xcd combine
+// workgroups on each XCD (none free: the launch finds no slot and runs unsplit). Lane
+// 8 * slot + x reads the slot's owner word and its count of XCD x; the slot is free when
+// all eight counts are where its last launch ends. A slot that last served this output is
+// taken first, so no second one ever carries its pointer. The exchange fails if another
+// launch was faster.
+__global__ __launch_bounds__(64) void split_claim_kernel(u16 *out, unsigned per_xcd)
 {
-    if (threadIdx.x != 0) return;
-    for (int i = 0; i < kSplitSlots; ++i) {
-        unsigned long long free_word = 0ull;
-        if (__hip_atomic_compare_exchange_strong(&split_control.owner[i], &free_word,
-                                                 (unsigned long long)(uintptr_t)out, __ATOMIC_ACQUIRE,
-                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-            return;
+    static_assert(kSplitSlots * kXcds == 64, "one lane per slot and XCD");
+    const int lane = threadIdx.x, slot = lane / kXcds, x = lane % kXcds;
+    const unsigned long long me = (unsigned long long)(uintptr_t)out;
+    for (int tries = 0; tries < 2 * kSplitSlots; ++tries) {
+        unsigned long long own =
+            __hip_atomic_load(&split_control.owner[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned count =
+            __hip_atomic_load(&split_control.done[slot][x][0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint64_t through = __builtin_amdgcn_ballot_w64((count & 0xFFFFu) == (unsigned)(own & 0xFFFFu));
+        const bool is_free = ((through >> (slot * kXcds)) & 0xFFu) == 0xFFu;
+        const uint64_t mine = __builtin_amdgcn_ballot_w64(is_free && own >> 16 == me);
+        const uint64_t any = __builtin_amdgcn_ballot_w64(is_free);
+        if (!any) return;
+        bool taken = false;
+        if (lane == (int)__builtin_ctzll(mine ? mine : any))
+            taken = __hip_atomic_compare_exchange_strong(&split_control.owner[slot], &own,
+                                                         me << 16 | ((own + per_xcd) & 0xFFFFu), __ATOMIC_RELAXED,
+                                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (__builtin_amdgcn_ballot_w64(taken)) return;
     }
 }
 
@@ -1117,19 +1139,12 @@ __global__ __launch_bounds__(kCombineThreads) void split_combine_kernel(int32_t 
             *reinterpret_cast<u32x2 *>(out + (tq * Hq + h) * D + d0) = __builtin_bit_cast(u32x2, bv);
         }
     }
-    // The last workgroup gives the slot back (every workgroup has looked it up and read
-    // its partial results by then).
+    // This workgroup is through with the slot: it only reads it, and every read has returned
+    // its value before the barrier.
     __syncthreads();
-    if (threadIdx.x == 0) {
-        // Relaxed: this kernel only reads the slot, and every read has returned its value
-        // before the barrier; the words below order themselves through the counter.
-        const unsigned before = __hip_atomic_fetch_add(&split_control.done[slot], 1u, __ATOMIC_RELAXED,
-                                                       __HIP_MEMORY_SCOPE_AGENT);
-        if (before + 1 == gridDim.x) {
-            __hip_atomic_store(&split_control.done[slot], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&split_control.owner[slot], 0ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-        }
-    }
+    if (threadIdx.x == 0)
+        __hip_atomic_fetch_add(&split_control.done[slot][blockIdx.x % kXcds][0], 1u, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
 }
 
 }  // namespace
@@ -1324,7 +1339,8 @@ hipError_t launch_group(const int32_t *seq, int n, const u16 *qq, const pcr_kv_p
         } else if (!chunk) {
             attn(std::integral_constant<int, kKeyHalves>{});
         } else {
-            hipLaunchKernelGGL(split_claim_kernel, dim3(1), dim3(64), 0, s, oo);
+            // (the grid is a multiple of the XCD count)
+            hipLaunchKernelGGL(split_claim_kernel, dim3(1), dim3(64), 0, s, oo, grid.x / kXcds);
             attn(std::integral_constant<int, kKeySplit>{});
             hipLaunchKernelGGL((split_combine_kernel<D>), grid, dim3(kCombineThreads), 0, s, Hkv, num_q_heads, T,
                                scale_log2, oo, wm);
@@ -1366,7 +1382,7 @@ hipError_t launch_prefix_prefill_attn(const void *q, const pcr_kv_pool &pool,
     // that need no merge are written beside them: not for outputs that overlap q.
     const uintptr_t qa = (uintptr_t)q, oa = (uintptr_t)out;
     const uintptr_t bytes = (uintptr_t)T * num_q_heads * pool.head_dim * 2;
-    const bool can_split = n_launch == 1 && (qa + bytes <= oa || oa + bytes <= qa);
+    const bool can_split = n_launch == 1 && oa >> 48 == 0 && (qa + bytes <= oa || oa + bytes <= qa);
     for (int l = 0; l < n_launch; ++l) {
         int n = 0;
         for (int k = l; k < n_act; k += n_launch) group[n++] = seq[k];
