@@ -1172,13 +1172,14 @@ void launch_attn(dim3 grid, hipStream_t s, const u16 *qq, const u16 *pk, const u
 // items still fit the compute units (and the scratch) in one round.
 // A key tile takes a workgroup 0.58 us with few compute units busy and 0.75-0.9 us with
 // all of them (the clock follows the power); the claim, the partial results and the
-// combine kernel together cost about 12 us, i.e. 20 tiles. So the split is taken when
-// the longest item has at least 4/3 chunk + 20 tiles. Measured (32 query / 8 kv heads of
-// 128, unsplit -> split): 43 new tokens on 7985 cached 77 -> 25 us; 16 on 2000 25.3 ->
-// 18; 128 on 4000 44.5 -> 27; 400 on 4000 47.4 -> 44; 2 on 16000 143 -> 26; 1024 on 15360
-// twice with 8 / 1 heads 150 -> 127. Near the line: 16 on 1300 19.5 -> 18.5, 512 on 4000
-// 48.5 -> 48.6 us. (Chunks of at least 4, 6, 8, 12 or 16 tiles: 4 to 8 alike, 12 and 16
-// up to 20% slower on prefixes of 2k.)
+// combine kernel together cost about 9 us, i.e. 14 tiles. So the split is taken when
+// the longest item has at least 4/3 chunk + 14 tiles. Measured (32 query / 8 kv heads of
+// 128, unsplit -> split): 43 new tokens on 7985 cached 77 -> 23 us; 16 on 2000 25 -> 18;
+// 128 on 4000 44.5 -> 24; 400 on 4000 47 -> 41; 2 on 16000 143 -> 25; 1024 on 15360
+// twice with 8 / 1 heads 150 -> 124. Near the line: 16 on 1250 18.8 -> 17.3, 512 on 4000
+// 48.9 -> 46, 640 on 4000 53 -> 52 us; 16 on 1100 (17.8 us) stays whole. (Chunks of at
+// least 4, 6, 8, 12 or 16 tiles: 4 to 8 alike, 12 and 16 up to 20% slower on prefixes
+// of 2k.)
 int32_t split_chunk(const int32_t *seq, int n, const int32_t *host_prefix_lens, const int32_t *host_cu_suffix, int G,
                     int Hkv, int n_cu)
 {
@@ -1196,7 +1197,7 @@ int32_t split_chunk(const int32_t *seq, int n, const int32_t *host_prefix_lens, 
         }
         return w * Hkv;
     };
-    int32_t lo = kSplitMinChunk, hi = (longest - 20) * 3 / 4;
+    int32_t lo = kSplitMinChunk, hi = (longest - 14) * 3 / 4;
     if (lo > hi || items(hi) > cap) return 0;
     while (lo < hi) {
         const int32_t mid = lo + (hi - lo) / 2;
