@@ -11,7 +11,7 @@
 //
 // Work decomposition. The key range of each (sequence, kv head) is cut into
 // n_split chunks of `chunk` keys (a multiple of 32). Each chunk is the work of
-// one wave (decode_wave::chunk, decode_wave.h: the G query heads as MFMA columns,
+// one wave (of two or four that merge in LDS when a batch is small: DecodePlan::sub) (decode_wave::chunk, decode_wave.h: the G query heads as MFMA columns,
 // K and V straight from HBM into registers, here with three register sets so that
 // two steps of loads are in flight while a third is used); the host picks n_split
 // so that every SIMD gets about one wave. Every byte is used once: V loads are
@@ -58,6 +58,9 @@ constexpr int kMaxCols = decode_wave::kMaxCols;   // query heads per kv head hel
 // two waves per SIMD with two sets each.
 constexpr int waves_per_cu(int) { return 4; }
 constexpr int kMinChunk = 256;         // keys; shorter chunks spend more on set-up than on loads
+// Waves that share one chunk of a small batch, at most: the chunks alone then give few of
+// the SIMDs a wave, each with eight or more serial steps.
+constexpr int kMaxSub = kWaves;
 constexpr float kLog2e = 1.4426950408889634f;
 
 template <int D, bool K_CACHED>
@@ -65,23 +68,27 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1))) v
     const u16 *__restrict__ q, const u16 *__restrict__ pool_k, const u16 *__restrict__ pool_v,
     int32_t num_blocks, int32_t Hkv, const int32_t *__restrict__ block_tables, int32_t max_blocks,
     const int32_t *__restrict__ context_lens, int32_t B, int32_t Hq, int32_t n_split, int32_t chunk,
-    float scale_log2, int32_t lds_merge, u16 *__restrict__ out, float *__restrict__ ws_o,
+    float scale_log2, int32_t lds_merge, int32_t sub, u16 *__restrict__ out, float *__restrict__ ws_o,
     float *__restrict__ ws_ml)
 {
     constexpr int MT = D / 16;    // V products (16 dims each)
     const int lane = (int)(threadIdx.x & 63);
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int wg_waves = (int)(blockDim.x >> 6);   // n_split when the chunks merge in LDS
-    const int64_t task = (int64_t)blockIdx.x * wg_waves + wave;
+    // A workgroup of sub > 1 waves shares one chunk and merges in LDS; otherwise each wave
+    // takes a chunk (all n_split of one sequence when those merge in LDS).
+    const int wg_waves = (int)(blockDim.x >> 6);
+    const int64_t task = sub > 1 ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * wg_waves + wave;
     if (task >= (int64_t)B * Hkv * n_split) return;   // never for a merging workgroup (exact grid)
     const int sp = (int)(task % n_split);
     const int bg = (int)(task / n_split);
     const int g = bg % Hkv, b = bg / Hkv;
     const int n_keys = context_lens[b];
-    const int kbeg = sp * chunk;
-    const bool active = kbeg < n_keys;             // wave-uniform
-    if (!active && !lds_merge) return;             // a merging wave stays for the barrier
-    const int kend = min(n_keys, kbeg + chunk);
+    const int c0 = sp * chunk, c1 = min(n_keys, c0 + chunk);   // the chunk's keys
+    if (c0 >= n_keys && !lds_merge) return;        // (a wave of a sequence that merges in LDS stays for the barrier)
+    const int part_keys = sub > 1 ? (chunk / sub + kStepKeys - 1) / kStepKeys * kStepKeys : chunk;
+    const int kbeg = c0 + (sub > 1 ? wave * part_keys : 0);
+    const int kend = min(c1, kbeg + part_keys);
+    const bool active = kbeg < c1;                 // wave-uniform
     const int last_blk = max(0, min((n_keys - 1) >> 4, max_blocks - 1));   // last block with a visible key
     const int G = Hq / Hkv;
     const int c = lane & 15, q4 = lane >> 4;
@@ -101,11 +108,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1))) v
 
     float l_tot = l_run + __shfl_xor(l_run, 16);
     l_tot += __shfl_xor(l_tot, 32);
-    if (lds_merge) {
-        // The workgroup holds every chunk of one (sequence, kv head). Waves 1.. leave
-        // their O (lane layout), max and sum in LDS; wave 0 merges and writes. A chunk
-        // past the sequence's end contributes max -inf, sum 0, O 0; chunk 0 always has
-        // keys, so the merged max is finite.
+    if (lds_merge || sub > 1) {
+        // The workgroup holds every chunk of one (sequence, kv head), or every part of one
+        // chunk. Waves 1.. leave their O (lane layout), max and sum in LDS; wave 0 merges and
+        // writes. A part past the end contributes max -inf, sum 0, O 0; the first always
+        // has keys, so the merged max is finite.
         extern __shared__ f32x4 part_o[];          // [wave][MT][64 lanes]
         f32x2 *part_ml = reinterpret_cast<f32x2 *>(part_o + wg_waves * MT * 64);   // [wave][64 lanes]
         if (wave > 0) {
@@ -118,6 +125,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1))) v
         float M = m_run;
         for (int w = 1; w < wg_waves; ++w) M = fmaxf(M, part_ml[w * 64 + lane][0]);
         const float a0 = __builtin_amdgcn_exp2f(m_run - M);
+        m_run = M;
         l_tot *= a0;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) o[mt] *= a0;
@@ -130,7 +138,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1))) v
         }
     }
     if (!col) return;
-    if (lds_merge || (kbeg == 0 && kend == n_keys)) {   // merged, or the only chunk of its sequence
+    if (lds_merge || (c0 == 0 && c1 == n_keys)) {   // merged, or the only chunk of its sequence
         const float inv = 1.f / l_tot;
         u16 *orow = out + ((int64_t)b * Hq + h) * D + 4 * q4;
 #pragma unroll
@@ -316,6 +324,21 @@ DecodePlan decode_plan(int32_t B, int32_t num_q_heads, int32_t num_kv_heads, int
     // has in flight) ordinary K loads, which fetch each K line once per step.
     bool same = ctx != nullptr;
     for (int32_t b = 0; b < B && same; ++b) same = ctx[b] == max_context;
+    // Chunks that merge through the workspace and leave SIMDs idle are shared by two or four
+    // waves each (whole steps), which merge in LDS: the partial results stay as many, and a
+    // wave has a quarter of the serial steps. Measured (32 query / 8 kv heads of 128): one
+    // context of 4000 keys 17.8 -> 11.8 us, of 8000 19.8 -> 14.2, of 16000 (two waves) 22.3 ->
+    // 21.1, four of 500-2500 18.1 -> 12.0. (Chunks of 128 keys instead, twice the partial
+    // results: 15.5 at 4000 keys, 24-27 at 16000.)
+    p.sub = 1;
+    if (ctx && p.workspace_bytes > 0) {
+        int64_t chunks = 0;
+        for (int32_t b = 0; b < B; ++b) chunks += ((int64_t)ctx[b] + p.chunk - 1) / p.chunk;
+        chunks *= num_kv_heads;
+        while (2 * p.sub <= kMaxSub && 2 * p.sub * chunks <= (int64_t)n_cu * waves_per_cu(head_dim) &&
+               p.chunk / (2 * p.sub) >= kStepKeys)
+            p.sub *= 2;
+    }
     p.k_streamed = same && (int64_t)B * num_kv_heads * p.n_split >= (int64_t)n_cu * waves_per_cu(head_dim);
     return p;
 }
@@ -333,9 +356,10 @@ hipError_t launch_decode_attn(const void *q, const pcr_kv_pool &pool, const int3
     // decode_combine_kernel (a chunk past its sequence's end then ends its wave at once).
     const int lds_merge = plan.lds_merge;
     const bool through_ws = plan.n_split > 1 && !lds_merge;
-    const int wg_waves = through_ws ? plan.ws_wg_waves : plan.n_split;
-    const dim3 grid((unsigned)((n_tasks + wg_waves - 1) / wg_waves));
-    const size_t lds = lds_merge ? (size_t)wg_waves * 64 * ((D / 16) * 16 + 8) : 0;
+    const int sub = through_ws ? plan.sub : 1;
+    const int wg_waves = sub > 1 ? sub : through_ws ? plan.ws_wg_waves : plan.n_split;
+    const dim3 grid((unsigned)(sub > 1 ? n_tasks : (n_tasks + wg_waves - 1) / wg_waves));
+    const size_t lds = lds_merge || sub > 1 ? (size_t)wg_waves * 64 * ((D / 16) * 16 + 8) : 0;
     float *ws_o = through_ws ? static_cast<float *>(workspace) : nullptr;
     float *ws_ml = through_ws ? ws_o + n_tasks * G * D : nullptr;
     const float scale_log2 = sm_scale * kLog2e;
@@ -345,7 +369,7 @@ hipError_t launch_decode_attn(const void *q, const pcr_kv_pool &pool, const int3
     auto *oo = static_cast<u16 *>(out);
     auto split = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, grid, dim3(64 * wg_waves), lds, s, qq, pk, pv, pool.num_blocks, Hkv, block_tables,
-                           max_blocks, context_lens, B, num_q_heads, plan.n_split, plan.chunk, scale_log2, lds_merge,
+                           max_blocks, context_lens, B, num_q_heads, plan.n_split, plan.chunk, scale_log2, lds_merge, sub,
                            oo, ws_o, ws_ml);
     };
     if (D == 128) {

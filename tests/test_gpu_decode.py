@@ -345,3 +345,26 @@ def test_decode_loop_16_steps():
         _check(got, want, f"decode step {step} (decode entry point)")
     assert np.array_equal(u16(L.pool.k), pk) and np.array_equal(u16(L.pool.v), pv)
     assert all(t <= b.block_tables.shape[1] * BS for t in total)
+
+
+@pytest.mark.parametrize("ctx,Hq,Hkv,d", [
+    ([1281], 32, 8, 128), ([4000], 32, 8, 128), ([2600, 31, 1300], 8, 8, 64), ([16001], 16, 1, 128),
+    ([4097, 4096, 1, 2000], 32, 2, 64), ([5000] * 5, 20, 4, 128),
+])
+def test_decode_chunks_shared_by_several_waves(ctx, Hq, Hkv, d):
+    """Batches whose chunks give few of the SIMDs a wave: two or four waves share a chunk
+    (parts of whole 32-key steps, the last one short or empty), with NaN patterns in every
+    slot past a context."""
+    q, pk, pv, bt = _decode_inputs(ctx, Hq, Hkv, d, seed=90 + len(ctx) + d)
+    for b, n in enumerate(ctx):
+        if n % BS:
+            blk = bt[b][n // BS]
+            pk.reshape(-1, Hkv, BS, d)[blk, :, n % BS:] = 0xFFFF
+            pv.reshape(-1, Hkv, d, BS)[blk, :, :, n % BS:] = 0xFFFF
+    say(f"[gpu] decode shared chunks {ctx} Hq={Hq} Hkv={Hkv} d={d}")
+    need = pcr.decode_attn_workspace_bytes(len(ctx), Hq, Hkv, d, max(ctx))
+    ws = torch.empty(max(need, 16), dtype=torch.uint8, device="cuda")
+    out = _decode_gpu(q, pk, pv, bt, ctx, Hq, Hkv, d, workspace=ws)
+    got = synth.bf16_bits_to_f32(u16(out)).astype(np.float64)
+    assert np.all(np.isfinite(got))
+    _check(got, _decode_oracle(q, pk, pv, bt, ctx, Hkv), "decode shared chunks")
