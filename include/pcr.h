@@ -267,8 +267,9 @@ pcr_status pcr_prefix_prefill_attn(const void *q, const pcr_kv_pool *pool,
  *     less time when there are more workgroups than compute units, else key halves, for
  *     launches that leave compute units idle with the keys cut into chunks; pcr_pipeline_run and
  *     pcr_pipeline_run_offload, whose pull-kernel loads share the compute units
- *     with the attention, take key halves (shorter workgroups let the copy
- *     workgroups onto a compute unit sooner);
+ *     with the attention, take key halves unless the row-halves workgroups all fit the
+ *     compute units at once (shorter workgroups let the copy workgroups onto a compute
+ *     unit sooner), and never cut the keys;
  *   PCR_ATTN_SCHEDULE_KEY_HALVES: 128 packed query rows per workgroup, the two
  *     wave groups on the two halves of the key range, merged at the end;
  *   PCR_ATTN_SCHEDULE_ROW_HALVES: 256 packed query rows per workgroup, each wave

@@ -1254,11 +1254,12 @@ hipError_t launch_group(const int32_t *seq, int n, const u16 *qq, const pcr_kv_p
 {
     const int Hkv = pool.num_kv_heads, G = num_q_heads / Hkv;
     auto rows_of = [&](int32_t b) { return ((int64_t)host_cu_suffix[b + 1] - host_cu_suffix[b]) * G; };
-    int sched = g_schedule.load(std::memory_order_relaxed);
-    if (sched == PCR_ATTN_SCHEDULE_AUTO) sched = auto_schedule;
+    const int sched = g_schedule.load(std::memory_order_relaxed);
+    const bool prefer_keys = auto_schedule == PCR_ATTN_SCHEDULE_KEY_HALVES;
     // More key-halves items than compute units: row halves when they are estimated to take
     // less time (unless the caller prefers key halves, whose shorter workgroups free a
-    // compute unit sooner for copy kernels that share the device). Row halves win where
+    // compute unit sooner for copy kernels that share the device, and the row-halves items
+    // would not all fit the compute units at once). Row halves win where
     // both fill whole rounds; they lose where their fewer items leave more of the last
     // round idle, and where the suffixes are shorter than their tiles. Against taking them
     // from two items per compute unit on (32 query / 8 kv heads of 128): 64 sequences of 32
@@ -1267,17 +1268,21 @@ hipError_t launch_group(const int32_t *seq, int n, const u16 *qq, const pcr_kv_p
     // of 40 other shapes none lost 2%.
     bool rows = sched == PCR_ATTN_SCHEDULE_ROW_HALVES;
     if (sched == PCR_ATTN_SCHEDULE_AUTO) {
-        int64_t tiles = 0;   // row tiles of 128 rows, one kv head
-        for (int k = 0; k < n; ++k) tiles += (rows_of(seq[k]) + kRowsPerWG - 1) / kRowsPerWG;
+        int64_t tiles = 0, tiles2 = 0;   // row tiles of 128 and of 256 rows, one kv head
+        for (int k = 0; k < n; ++k) {
+            tiles += (rows_of(seq[k]) + kRowsPerWG - 1) / kRowsPerWG;
+            tiles2 += (rows_of(seq[k]) + 2 * kRowsPerWG - 1) / (2 * kRowsPerWG);
+        }
         auto time_of = [&](int rows_per_item) {
             return schedule_time(seq, n, host_prefix_lens, host_cu_suffix, G, Hkv, pool.head_dim, rows_per_item, n_cu);
         };
-        rows = tiles * Hkv > n_cu && time_of(2 * kRowsPerWG) < time_of(kRowsPerWG);
+        rows = tiles * Hkv > n_cu && (!prefer_keys || tiles2 * Hkv <= n_cu) &&
+               time_of(2 * kRowsPerWG) < time_of(kRowsPerWG);
     }
     const int64_t rpw = rows ? 2 * kRowsPerWG : kRowsPerWG;
     // Key tiles per item, 0: no key split.
     const int32_t chunk =
-        sched == PCR_ATTN_SCHEDULE_AUTO && !rows && can_split
+        sched == PCR_ATTN_SCHEDULE_AUTO && !prefer_keys && !rows && can_split
             ? split_chunk(seq, n, host_prefix_lens, host_cu_suffix, G, Hkv, n_cu)
             : 0;
     auto keys_of = [&](int32_t b) { return host_prefix_lens[b] + host_cu_suffix[b + 1] - host_cu_suffix[b]; };

@@ -105,7 +105,8 @@ pcr_status offload_with(const pcr_kv_pool *src, const int32_t *src_blocks, const
 
 // pcr_prefix_prefill_attn with a schedule preference: when the process-wide schedule
 // is PCR_ATTN_SCHEDULE_AUTO, auto_schedule PCR_ATTN_SCHEDULE_KEY_HALVES takes key
-// halves whatever the size (PCR_ATTN_SCHEDULE_AUTO: the size rule).
+// halves, unless row halves are estimated to be faster and their items all fit the compute
+// units at once (PCR_ATTN_SCHEDULE_AUTO: the rule without that limit, and the key split).
 pcr_status prefix_prefill_attn(const void *q, const pcr_kv_pool *pool, const int32_t *block_tables,
                                int32_t max_blocks, const int32_t *prefix_lens, const int32_t *cu_suffix,
                                const int32_t *host_prefix_lens, const int32_t *host_cu_suffix, int32_t B,

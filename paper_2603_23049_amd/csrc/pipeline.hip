@@ -209,7 +209,7 @@ pcr_status run_pipeline(const pcr_layer_io *layers, const pcr_host_kv *offload_d
         st = pcr_append_kv(&layers[l].pool, layers[l].k_new, layers[l].v_new, batch->slot_mapping,
                                       batch->T, compute_stream);
         if (st) return st;
-        // Beside pull-kernel loads the attention takes key halves: its shorter workgroups
+        // Beside pull-kernel loads the attention prefers key halves: its shorter workgroups
         // let a load's copy workgroups onto a compute unit sooner.
         st = prefix_prefill_attn(layers[l].q, &layers[l].pool, batch->block_tables, batch->max_blocks,
                                  batch->prefix_lens, batch->cu_suffix, batch->host_prefix_lens,
