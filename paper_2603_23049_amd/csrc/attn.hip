@@ -1118,16 +1118,19 @@ __global__ __launch_bounds__(kCombineThreads) void split_combine_kernel(int32_t 
                         ml[i] = pml[pt * (kSplitPartML / 8) + wg * 64 + lane];
                         o[i] = po[pt * (kSplitPartO / 16) + pc * 64 + lane];
                     }
-                    float Mn = M;                    // finite from the first pass: chunk 0 has keys of every row
+                    // -inf after a pass only if every score so far is (overflowed products): its
+                    // chunks then weigh 0, as in an unsplit launch
+                    float Mn = M;
 #pragma unroll
                     for (int i = 0; i < W; ++i) Mn = fmaxf(Mn, ml[i][0]);
-                    const float r = __builtin_amdgcn_exp2f((M - Mn) * c);   // 0 on the first pass
+                    const float r = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((M - Mn) * c);
                     M = Mn;
                     L *= r;
                     acc *= r;
 #pragma unroll
                     for (int i = 0; i < W; ++i) {
-                        const float w = k0 + i < ns ? __builtin_amdgcn_exp2f((ml[i][0] - M) * c) : 0.f;
+                        const float w = k0 + i < ns && ml[i][0] != -INFINITY
+                                            ? __builtin_amdgcn_exp2f((ml[i][0] - M) * c) : 0.f;
                         L += w * ml[i][1];
                         acc += w * o[i];
                     }

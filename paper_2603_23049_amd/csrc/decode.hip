@@ -11,9 +11,10 @@
 //
 // Work decomposition. The key range of each (sequence, kv head) is cut into
 // n_split chunks of `chunk` keys (a multiple of 32). Each chunk is the work of
-// one wave (of two or four that merge in LDS when a batch is small: DecodePlan::sub) (decode_wave::chunk, decode_wave.h: the G query heads as MFMA columns,
-// K and V straight from HBM into registers, here with three register sets so that
-// two steps of loads are in flight while a third is used); the host picks n_split
+// one wave, or of two or four that merge in LDS when a batch is small (DecodePlan::sub).
+// A wave (decode_wave::chunk, decode_wave.h) holds the G query heads as MFMA columns and
+// takes K and V straight from HBM into registers, here with three register sets so that
+// two steps of loads are in flight while a third is used; the host picks n_split
 // so that every SIMD gets about one wave. Every byte is used once: V loads are
 // non-temporal, and K loads too when every sequence has one length and the chunks
 // give every SIMD a wave (the kernel then streams HBM at full rate, where bypassing
@@ -369,8 +370,8 @@ hipError_t launch_decode_attn(const void *q, const pcr_kv_pool &pool, const int3
     auto *oo = static_cast<u16 *>(out);
     auto split = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, grid, dim3(64 * wg_waves), lds, s, qq, pk, pv, pool.num_blocks, Hkv, block_tables,
-                           max_blocks, context_lens, B, num_q_heads, plan.n_split, plan.chunk, scale_log2, lds_merge, sub,
-                           oo, ws_o, ws_ml);
+                           max_blocks, context_lens, B, num_q_heads, plan.n_split, plan.chunk, scale_log2, lds_merge,
+                           sub, oo, ws_o, ws_ml);
     };
     if (D == 128) {
         if (plan.k_streamed) split(decode_split_kernel<128, false>); else split(decode_split_kernel<128, true>);

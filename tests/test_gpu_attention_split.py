@@ -136,6 +136,27 @@ def test_output_in_place_of_the_queries_is_not_split():
     assert torch.equal(q.view(torch.int16), whole)
 
 
+@pytest.mark.parametrize("low", [100, 6000])
+def test_keys_whose_products_overflow_weigh_nothing(low):
+    """The first keys' products overflow to -inf: whole chunks, and a whole pass of the
+    merge, carry no weight, and the rows come from the other keys (as without chunks)."""
+    L, _, _ = _layer([9000], [3], 4, 1, 128, seed=51)
+    say(f"[gpu] key split, {low} keys at -inf")
+    L.q.copy_(L.q.view(torch.bfloat16).abs().view(L.q.dtype))
+    k = L.pool.k.view(torch.bfloat16).view(-1, 1, BS, 128)
+    for t in range(0, low, BS):
+        k[L.bt[0, t // BS].long(), 0, :min(BS, low - t)] = -3e38
+    L.attn()
+    torch.cuda.synchronize()
+    got = L.out_f64()
+    assert np.all(np.isfinite(got))
+    with attn_schedule("key_halves"):
+        L.attn()
+    torch.cuda.synchronize()
+    mx, mean = error_stats(got, L.out_f64())
+    assert mx <= MAX_ABS and mean <= MEAN_ABS, f"max {mx} mean {mean}"
+
+
 @pytest.mark.parametrize("pl,sl,G,Hkv,d", [
     ([300] * 64, [20] * 64, 4, 8, 128),            # suffixes shorter than a tile: key halves
     ([700], [1280], 4, 8, 128), ([40] * 5, [700] * 5, 4, 8, 64),
