@@ -69,16 +69,18 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1))) v
     const u16 *__restrict__ q, const u16 *__restrict__ pool_k, const u16 *__restrict__ pool_v,
     int32_t num_blocks, int32_t Hkv, const int32_t *__restrict__ block_tables, int32_t max_blocks,
     const int32_t *__restrict__ context_lens, int32_t B, int32_t Hq, int32_t n_split, int32_t chunk,
-    float scale_log2, int32_t lds_merge, int32_t sub, u16 *__restrict__ out, float *__restrict__ ws_o,
+    float scale_log2, int32_t lds_merge, int32_t part_keys, u16 *__restrict__ out, float *__restrict__ ws_o,
     float *__restrict__ ws_ml)
 {
     constexpr int MT = D / 16;    // V products (16 dims each)
     const int lane = (int)(threadIdx.x & 63);
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    // A workgroup of sub > 1 waves shares one chunk and merges in LDS; otherwise each wave
-    // takes a chunk (all n_split of one sequence when those merge in LDS).
+    // A workgroup whose waves share one chunk (part_keys of it each) merges in LDS; otherwise
+    // each wave takes a chunk (all n_split of one sequence when those merge in LDS).
+    // part_keys comes from the host, so that no wave divides for it.
+    const bool shared = part_keys < chunk;
     const int wg_waves = (int)(blockDim.x >> 6);
-    const int64_t task = sub > 1 ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * wg_waves + wave;
+    const int64_t task = shared ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * wg_waves + wave;
     if (task >= (int64_t)B * Hkv * n_split) return;   // never for a merging workgroup (exact grid)
     const int sp = (int)(task % n_split);
     const int bg = (int)(task / n_split);
@@ -86,8 +88,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1))) v
     const int n_keys = context_lens[b];
     const int c0 = sp * chunk, c1 = min(n_keys, c0 + chunk);   // the chunk's keys
     if (c0 >= n_keys && !lds_merge) return;        // (a wave of a sequence that merges in LDS stays for the barrier)
-    const int part_keys = sub > 1 ? (chunk / sub + kStepKeys - 1) / kStepKeys * kStepKeys : chunk;
-    const int kbeg = c0 + (sub > 1 ? wave * part_keys : 0);
+    const int kbeg = c0 + (shared ? wave * part_keys : 0);
     const int kend = min(c1, kbeg + part_keys);
     const bool active = kbeg < c1;                 // wave-uniform
     const int last_blk = max(0, min((n_keys - 1) >> 4, max_blocks - 1));   // last block with a visible key
@@ -109,7 +110,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1))) v
 
     float l_tot = l_run + __shfl_xor(l_run, 16);
     l_tot += __shfl_xor(l_tot, 32);
-    if (lds_merge || sub > 1) {
+    if (lds_merge || shared) {
         // The workgroup holds every chunk of one (sequence, kv head), or every part of one
         // chunk. Waves 1.. leave their O (lane layout), max and sum in LDS; wave 0 merges and
         // writes. A part past the end contributes max -inf, sum 0, O 0; the first always
@@ -358,6 +359,8 @@ hipError_t launch_decode_attn(const void *q, const pcr_kv_pool &pool, const int3
     const int lds_merge = plan.lds_merge;
     const bool through_ws = plan.n_split > 1 && !lds_merge;
     const int sub = through_ws ? plan.sub : 1;
+    // Keys of a wave that shares its chunk, whole steps (below the chunk: it has at least 2 * 32).
+    const int part_keys = sub > 1 ? (plan.chunk / sub + kStepKeys - 1) / kStepKeys * kStepKeys : plan.chunk;
     const int wg_waves = sub > 1 ? sub : through_ws ? plan.ws_wg_waves : plan.n_split;
     const dim3 grid((unsigned)(sub > 1 ? n_tasks : (n_tasks + wg_waves - 1) / wg_waves));
     const size_t lds = lds_merge || sub > 1 ? (size_t)wg_waves * 64 * ((D / 16) * 16 + 8) : 0;
@@ -371,7 +374,7 @@ hipError_t launch_decode_attn(const void *q, const pcr_kv_pool &pool, const int3
     auto split = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, grid, dim3(64 * wg_waves), lds, s, qq, pk, pv, pool.num_blocks, Hkv, block_tables,
                            max_blocks, context_lens, B, num_q_heads, plan.n_split, plan.chunk, scale_log2, lds_merge,
-                           sub, oo, ws_o, ws_ml);
+                           part_keys, oo, ws_o, ws_ml);
     };
     if (D == 128) {
         if (plan.k_streamed) split(decode_split_kernel<128, false>); else split(decode_split_kernel<128, true>);
