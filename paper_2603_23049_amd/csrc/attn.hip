@@ -269,7 +269,7 @@ __device__ __forceinline__ void decode_workgroup(const u16 *__restrict__ q, cons
     const bool col = c < G;
     const int h = g * G + c;
     f32x4 o[MT];
-    float m_run = -INFINITY, l_run = 0.f;
+    float m_run = decode_wave::kNoMax, l_run = 0.f;
     if (kbeg < n_keys) {
         const u16 *qrow = q + (t0 * Hq + (col ? h : g * G)) * D + 8 * q4;
         decode_wave::chunk<D, 2, true>(qrow, col, pool_k, pool_v, num_blocks, Hkv, g, bt_row, last_blk, kbeg, kend,
@@ -281,7 +281,7 @@ __device__ __forceinline__ void decode_workgroup(const u16 *__restrict__ q, cons
     float l_tot = l_run + __shfl_xor(l_run, 16);
     l_tot += __shfl_xor(l_tot, 32);
     // Waves 1.. leave O (lane layout), max and sum in LDS; wave 0 merges and writes. A
-    // chunk past the end contributes max -inf, sum 0, O 0; chunk 0 always has keys.
+    // chunk past the end, or without a finite score, contributes max kNoMax, sum 0, O 0.
     f32x4 *part_o = reinterpret_cast<f32x4 *>(lds);                         // [wave][MT][64 lanes]
     float *part_ml = reinterpret_cast<float *>(part_o + kWaves * MT * 64);   // [wave][64 lanes][2]
     if (wave > 0) {

@@ -98,7 +98,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1))) v
     const int h = g * G + c;
 
     f32x4 o[MT];
-    float m_run = -INFINITY, l_run = 0.f;
+    float m_run = decode_wave::kNoMax, l_run = 0.f;
     if (active) {
         const u16 *qrow = q + ((int64_t)b * Hq + (col ? h : g * G)) * D + 8 * q4;
         decode_wave::chunk<D, 3, K_CACHED>(qrow, col, pool_k, pool_v, num_blocks, Hkv, g, block_tables + (int64_t)b * max_blocks,
@@ -113,8 +113,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1))) v
     if (lds_merge || shared) {
         // The workgroup holds every chunk of one (sequence, kv head), or every part of one
         // chunk. Waves 1.. leave their O (lane layout), max and sum in LDS; wave 0 merges and
-        // writes. A part past the end contributes max -inf, sum 0, O 0; the first always
-        // has keys, so the merged max is finite.
+        // writes. A part past the end, or without a finite score, contributes max kNoMax,
+        // sum 0, O 0; every max is finite.
         extern __shared__ f32x4 part_o[];          // [wave][MT][64 lanes]
         f32x2 *part_ml = reinterpret_cast<f32x2 *>(part_o + wg_waves * MT * 64);   // [wave][64 lanes]
         if (wave > 0) {
@@ -189,7 +189,7 @@ __global__ __launch_bounds__(kThreads) void decode_combine_kernel(
         float mb = ml[0];
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) mb = fmaxf(mb, __shfl_xor(mb, off));
-        const float Mn = fmaxf(M, mb);                  // finite: chunk k0 has keys
+        const float Mn = fmaxf(M, mb);                  // finite: every chunk's max is
         const float r = __builtin_amdgcn_exp2f(M - Mn);  // 0 on the first pass
         M = Mn;
         const float w = __builtin_amdgcn_exp2f(ml[0] - M);   // 0 past the last chunk

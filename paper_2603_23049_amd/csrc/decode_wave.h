@@ -39,6 +39,10 @@ typedef unsigned short u16;
 
 constexpr int kStepKeys = 32;   // keys per step: two pool blocks
 constexpr int kMaxCols = 16;    // query heads per kv head that one wave's tiles hold
+// The running max before any finite score: the lowest finite value, so that a difference of
+// two of them is 0 and never inf - inf. A range whose products all overflow to -inf (or
+// that is empty) keeps it, with sum 0 and O 0, and weighs nothing beside any real score.
+constexpr float kNoMax = -__FLT_MAX__;
 
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 
@@ -98,7 +102,7 @@ __device__ __forceinline__ void chunk(const u16 *__restrict__ qrow, bool col, co
             R.v[mt] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(vp + 16 * mt * kBlockSize));
     };
 
-    m_run = -INFINITY;
+    m_run = kNoMax;
     l_run = 0.f;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) o[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -126,7 +130,7 @@ __device__ __forceinline__ void chunk(const u16 *__restrict__ qrow, bool col, co
                          fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3])));
         mx = fmaxf(mx, __shfl_xor(mx, 16));
         mx = fmaxf(mx, __shfl_xor(mx, 32));
-        const float m_new = fmaxf(m_run, mx * scale_log2);   // finite: key k0 is visible
+        const float m_new = fmaxf(m_run, mx * scale_log2);   // at least kNoMax: finite also where mx is -inf
         const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
         m_run = m_new;
         bf16x8 pb;
