@@ -248,7 +248,8 @@ pcr_status pcr_append_kv(const pcr_kv_pool *pool, const void *k_new, const void 
  * the same numerics. The partial results go to scratch the library holds per device
  * (eight launches' worth, about 140 MB, until the process ends); a launch takes its
  * part when it runs and gives it back, so calls on any streams and threads and replays
- * of captured graphs may overlap, each with its own out as ever. The chunks follow
+ * of captured graphs may overlap. (Calls that overlap may write one out only if they
+ * write equal values, as ever; each still has its own scratch.) The chunks follow
  * from the lengths alone, so repeated calls give identical bits; a launch that finds
  * eight others holding the scratch runs without chunks (same numerics, other roundings).
  */
@@ -286,6 +287,15 @@ pcr_status pcr_prefix_prefill_attn(const void *q, const pcr_kv_pool *pool,
 #define PCR_ATTN_SCHEDULE_KEY_HALVES 1
 #define PCR_ATTN_SCHEDULE_ROW_HALVES 2
 pcr_status pcr_prefill_attn_set_schedule(int32_t schedule);
+
+/*
+ * pcr_prefill_attn_hold_scratch -- a testing control, not part of the method: gives back
+ * the parts of the current device's key-split scratch that an earlier call holds, then
+ * holds n of the eight, so that launches find fewer or none. *free_entries is the number
+ * of launches that could register now: 64 with nothing running or held, the first eight
+ * of them with scratch. Synchronises the device; no other launch may be running.
+ */
+pcr_status pcr_prefill_attn_hold_scratch(int32_t n, int32_t *free_entries);
 
 /*
  * pcr_decode_attn -- one decode step: attention of one new query token per

@@ -49,6 +49,7 @@
 // each lane, since a direct load writes lane l's 16 bytes at base + 16*l.
 #include <algorithm>
 #include <atomic>
+#include <mutex>
 #include <type_traits>
 #include <vector>
 
@@ -187,6 +188,7 @@ struct AttnWorkMap {
     int32_t n_seq;                      // slots in use (sequences with new tokens)
     int32_t per_head;                   // work items of all sequences, one kv head
     int32_t chunk;                      // key split: 64-key tiles per item (else unused)
+    uint64_t launch;                    // key split: the launch's number (else unused)
     int32_t seq[kMaxMapSeqs];           // sequence in each slot
     int32_t tiles_end[kMaxMapSeqs];     // items of the slots up to and including this one
     int32_t prefix[kMaxMapSeqs];        // the slot's cached tokens p
@@ -200,37 +202,46 @@ enum AttnMode { kKeyHalves = 0, kRowHalves = 1, kKeySplit = 2 };
 // Scratch of key-split launches: kSplitSlots slots of kSplitParts partial results per
 // device, held until the process ends. A launch owns one slot from its claim kernel until
 // every workgroup of its combine kernel has counted itself out. The slot's owner word
-// holds the launch's output pointer, which names the launch: two launches in flight never
-// write one output, so the workgroups find their slot by looking for it, and nothing
-// about it is fixed on the host (launches on any streams and threads, and replays of
-// captured graphs, claim theirs when they run). With every slot taken a launch runs
-// unsplit.
+// holds the launch's number, which the host gives every enqueued launch: the workgroups
+// find their slot by looking for it, and which one it is is not fixed on the host
+// (launches on any streams and threads, and replays of captured graphs, claim theirs when
+// they run). The number and not the output pointer names the launch, since calls that
+// overlap may share an output (equal calls on two streams, say). With every slot taken a
+// launch runs unsplit.
+// Replays of one captured launch have one number, and HIP lets them overlap. They take
+// turns to claim (replay_lock), and one that finds its number in use joins: both write the
+// same partial results, and the entry is free when both are through. One that finds no
+// slot takes one of the entries past the slots, which have no scratch, so that a replay
+// that starts beside it runs unsplit too.
 constexpr int kSplitSlots = 8;
+constexpr int kSplitEntries = 64;                        // the slots, then entries without scratch
 constexpr int kSplitMinChunk = 4;                        // key tiles of an item, at least
 constexpr int kSplitParts = 256;                         // items of one launch, at most
 constexpr int kSplitPartO = kRowsPerWG * 128 * 4;        // bytes: O of 128 rows x 128 dims, fp32
 constexpr int kSplitPartML = kRowsPerWG * 2 * 8;         // bytes: (max, sum) per lane of 4 waves
 struct SplitControl {
-    // Output pointer of the slot's last launch (48 bits) and, below it, the counts at which
-    // that launch is through (16 bits). A claim exchanges the word as a whole.
-    unsigned long long owner[kSplitSlots];
+    // Number of the entry's last launch (48 bits) and, below it, the counts at which that
+    // launch is through (16 bits). A claim exchanges the word as a whole.
+    unsigned long long owner[kSplitEntries];
     // Combine workgroups that are through, of all launches so far, per XCD. Each count has
     // a line to itself: 256 workgroups counting at one address took 2-3 us, and the end of
     // a launch does not wait for a count to come back.
-    unsigned int done[kSplitSlots][kXcds][32];
+    unsigned int done[kSplitEntries][kXcds][32];
+    unsigned int replay_lock;
 };
 __device__ SplitControl split_control;
 __device__ __attribute__((aligned(1024))) char split_o[kSplitSlots][kSplitParts][kSplitPartO];
 __device__ __attribute__((aligned(1024))) char split_ml[kSplitSlots][kSplitParts][kSplitPartML];
 
-// The slot owned by the launch with this output (wave-uniform), or -1.
-__device__ __forceinline__ int split_slot(const u16 *out)
+// The entry owned by the launch with this number (wave-uniform), or -1. From kSplitSlots on
+// it has no scratch.
+__device__ __forceinline__ int split_entry(uint64_t launch)
 {
     const int lane = threadIdx.x & 63;
+    static_assert(kSplitEntries == 64, "one lane per entry");
     const unsigned long long own =
-        lane < kSplitSlots ? __hip_atomic_load(&split_control.owner[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                           : 0ull;
-    const uint64_t mine = __builtin_amdgcn_ballot_w64(own >> 16 == (unsigned long long)(uintptr_t)out);
+        __hip_atomic_load(&split_control.owner[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint64_t mine = __builtin_amdgcn_ballot_w64(own >> 16 == launch);
     return mine ? (int)__builtin_ctzll(mine) : -1;
 }
 
@@ -441,9 +452,10 @@ __global__ __launch_bounds__(kThreads) void prefill_attn_kernel(
         const int ns = (key_tiles(p + s - 1) + wm.chunk - 1) / wm.chunk;
         rt = it.local / ns;
         sp = it.local - rt * ns;
-        const int slot = split_slot(out);
-        if (slot < 0 && sp > 0) return;              // unsplit: chunk 0 takes every key
-        if (slot >= 0) part = slot * kSplitParts + g * wm.per_head + it.j;
+        const int slot = split_entry(wm.launch);
+        const bool whole = slot < 0 || slot >= kSplitSlots;
+        if (whole && sp > 0) return;                 // unsplit: chunk 0 takes every key
+        if (!whole) part = slot * kSplitParts + g * wm.per_head + it.j;
     }
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int grp = wave >> 2;              // key halves: which half of the keys; row halves: of the rows
@@ -1020,17 +1032,15 @@ __global__ __launch_bounds__(kThreads) void prefill_attn_kernel(
     store_rows<MH * 32, D>(stage, lane, orow, out, my0 * 32);
 }
 
-// One wave: takes a free slot for the launch with this output and per_xcd combine
-// workgroups on each XCD (none free: the launch finds no slot and runs unsplit). Lane
-// 8 * slot + x reads the slot's owner word and its count of XCD x; the slot is free when
-// all eight counts are where its last launch ends. A slot that last served this output is
-// taken first, so no second one ever carries its pointer. The exchange fails if another
-// launch was faster.
-__global__ __launch_bounds__(64) void split_claim_kernel(u16 *out, unsigned per_xcd)
+// One wave: takes a free slot for the launch with this number, which no other launch has,
+// and per_xcd combine workgroups on each XCD (none free: the launch finds no slot and runs
+// unsplit). Lane 8 * slot + x reads the slot's owner word and its count of XCD x; the slot
+// is free when all eight counts are where its last launch ends. The exchange fails if
+// another launch was faster.
+__global__ __launch_bounds__(64) void split_claim_kernel(uint64_t launch, unsigned per_xcd)
 {
     static_assert(kSplitSlots * kXcds == 64, "one lane per slot and XCD");
     const int lane = threadIdx.x, slot = lane / kXcds, x = lane % kXcds;
-    const unsigned long long me = (unsigned long long)(uintptr_t)out;
     for (int tries = 0; tries < 2 * kSplitSlots; ++tries) {
         unsigned long long own =
             __hip_atomic_load(&split_control.owner[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1038,16 +1048,78 @@ __global__ __launch_bounds__(64) void split_claim_kernel(u16 *out, unsigned per_
             __hip_atomic_load(&split_control.done[slot][x][0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const uint64_t through = __builtin_amdgcn_ballot_w64((count & 0xFFFFu) == (unsigned)(own & 0xFFFFu));
         const bool is_free = ((through >> (slot * kXcds)) & 0xFFu) == 0xFFu;
-        const uint64_t mine = __builtin_amdgcn_ballot_w64(is_free && own >> 16 == me);
         const uint64_t any = __builtin_amdgcn_ballot_w64(is_free);
         if (!any) return;
         bool taken = false;
-        if (lane == (int)__builtin_ctzll(mine ? mine : any))
+        if (lane == (int)__builtin_ctzll(any))
             taken = __hip_atomic_compare_exchange_strong(&split_control.owner[slot], &own,
-                                                         me << 16 | ((own + per_xcd) & 0xFFFFu), __ATOMIC_RELAXED,
-                                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                                                         launch << 16 | ((own + per_xcd) & 0xFFFFu),
+                                                         __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                         __HIP_MEMORY_SCOPE_AGENT);
         if (__builtin_amdgcn_ballot_w64(taken)) return;
     }
+}
+
+// The same for a captured launch, whose number its replays share: an entry in use under that
+// number (it is then through when this replay's workgroups are too: its end moves on by
+// them), else the slot an earlier replay had, else the first free entry, slots first. One
+// entry at most carries the number. The lock keeps two replays from taking an entry each;
+// whoever holds it is a running wave that waits for nothing, and the tries, far more than
+// 64 claims take, are bounded all the same (a wave that gives up leaves its launch
+// unsplit). Lane: entry.
+__global__ __launch_bounds__(64) void split_claim_replay_kernel(uint64_t launch, unsigned per_xcd)
+{
+    const int lane = threadIdx.x;
+    bool locked = false;
+    for (int tries = 0; tries < (1 << 14) && !locked; ++tries) {
+        unsigned open = 0u;
+        bool got = false;
+        if (lane == 0)
+            got = __hip_atomic_compare_exchange_strong(&split_control.replay_lock, &open, 1u, __ATOMIC_ACQUIRE,
+                                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        locked = __builtin_amdgcn_ballot_w64(got) != 0;
+        if (!locked) __builtin_amdgcn_s_sleep(8);
+    }
+    if (!locked) return;
+    bool done = false;
+    for (int tries = 0; tries < 2 * kSplitEntries && !done; ++tries) {
+        unsigned long long own =
+            __hip_atomic_load(&split_control.owner[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        bool is_free = true;
+#pragma unroll
+        for (int x = 0; x < kXcds; ++x) {
+            const unsigned count =
+                __hip_atomic_load(&split_control.done[lane][x][0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            is_free = is_free && (count & 0xFFFFu) == (unsigned)(own & 0xFFFFu);
+        }
+        const uint64_t mine = __builtin_amdgcn_ballot_w64(own >> 16 == launch);
+        const uint64_t free_entries = __builtin_amdgcn_ballot_w64(is_free);
+        const bool keep = (mine & ~free_entries) != 0 || (mine & ((1ull << kSplitSlots) - 1)) != 0;
+        const uint64_t any = keep ? mine : free_entries;
+        bool taken = false;
+        // An earlier replay's entry without scratch, free now: another one is taken, unless it
+        // is the first free one itself. (Only replays change these, so it is as it was read.)
+        if (!keep && mine && any && lane == (int)__builtin_ctzll(mine) && lane != (int)__builtin_ctzll(any))
+            __hip_atomic_store(&split_control.owner[lane], own & 0xFFFFu, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (any && lane == (int)__builtin_ctzll(any))
+            taken = __hip_atomic_compare_exchange_strong(&split_control.owner[lane], &own,
+                                                         launch << 16 | ((own + per_xcd) & 0xFFFFu),
+                                                         __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                         __HIP_MEMORY_SCOPE_AGENT);
+        done = !any || __builtin_amdgcn_ballot_w64(taken) != 0;
+    }
+    if (lane == 0)
+        __hip_atomic_store(&split_control.replay_lock, 0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// One wave: gives back the slot of a launch whose combine kernel does not run (it could not
+// be enqueued), by the counts that kernel would have added. No entry: nothing.
+__global__ __launch_bounds__(64) void split_release_kernel(uint64_t launch, unsigned per_xcd)
+{
+    const int slot = split_entry(launch);
+    if (slot >= 0 && threadIdx.x < kXcds)
+        __hip_atomic_fetch_add(&split_control.done[slot][threadIdx.x][0], per_xcd, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Merges the chunks of every row tile and decode row of a key-split launch:
@@ -1063,13 +1135,13 @@ __global__ __launch_bounds__(kCombineThreads) void split_combine_kernel(int32_t 
 {
     constexpr int MT = D / 32;
     constexpr int kCombineWaves = kCombineThreads / 64;
-    const int slot = split_slot(out);
+    const int slot = split_entry(wm.launch);
     if (slot < 0) return;                            // ran unsplit
     const Item it = locate_item(wm, Hkv);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int G = Hq / Hkv;
-    if (it.g < Hkv) {
+    if (it.g < Hkv && slot < kSplitSlots) {          // (past them: ran unsplit, counts itself out)
         const int p = it.p, s = it.s, rows_total = s * G;
         const int ns_seq = (key_tiles(p + s - 1) + wm.chunk - 1) / wm.chunk;
         const int rt = it.local / ns_seq, sp = it.local - rt * ns_seq;
@@ -1157,6 +1229,23 @@ int attn_rows_per_workgroup(int) { return kRowsPerWG; }
 namespace {
 // Schedule override (pcr_prefill_attn_set_schedule): 0 chooses per launch.
 std::atomic<int> g_schedule{PCR_ATTN_SCHEDULE_AUTO};
+
+// The number of a key-split launch: never one that an earlier launch of the process had
+// (48 bits are not used up).
+uint64_t next_launch()
+{
+    static std::atomic<uint64_t> n{0};
+    return n.fetch_add(1, std::memory_order_relaxed) + 1;
+}
+
+// Enqueues a kernel and returns this launch's own error (hipGetLastError may hold an older one).
+template <class T> struct Same { typedef T type; };   // (a parameter's type comes from the kernel alone)
+template <class... P>
+hipError_t enqueue(void (*kernel)(P...), dim3 grid, int threads, hipStream_t s, const typename Same<P>::type &...a)
+{
+    void *args[] = {const_cast<void *>(static_cast<const void *>(&a))...};
+    return hipLaunchKernel(reinterpret_cast<const void *>(kernel), grid, dim3(threads), args, 0, s);
+}
 
 template <int D, int MODE>
 void launch_attn(dim3 grid, hipStream_t s, const u16 *qq, const u16 *pk, const u16 *pv, const pcr_kv_pool &pool,
@@ -1333,11 +1422,12 @@ hipError_t launch_group(const int32_t *seq, int n, const u16 *qq, const pcr_kv_p
     wm.n_seq = n;
     wm.per_head = cum;
     wm.chunk = chunk;
+    wm.launch = chunk ? next_launch() : 0;
     const int64_t n_items = (Hkv % kXcds == 0) ? (int64_t)cum * Hkv : ((int64_t)cum * Hkv + kXcds - 1) / kXcds * kXcds;
     const dim3 grid((unsigned)n_items);
     auto *pk = static_cast<const u16 *>(pool.k);
     auto *pv = static_cast<const u16 *>(pool.v);
-    auto launch = [&](auto dim) {
+    auto launch = [&](auto dim) -> hipError_t {
         constexpr int D = decltype(dim)::value;
         auto attn = [&](auto mode) {
             launch_attn<D, decltype(mode)::value>(grid, s, qq, pk, pv, pool, block_tables, max_blocks, num_q_heads,
@@ -1348,20 +1438,72 @@ hipError_t launch_group(const int32_t *seq, int n, const u16 *qq, const pcr_kv_p
         } else if (!chunk) {
             attn(std::integral_constant<int, kKeyHalves>{});
         } else {
-            // (the grid is a multiple of the XCD count)
-            hipLaunchKernelGGL(split_claim_kernel, dim3(1), dim3(64), 0, s, oo, grid.x / kXcds);
-            attn(std::integral_constant<int, kKeySplit>{});
-            hipLaunchKernelGGL((split_combine_kernel<D>), grid, dim3(kCombineThreads), 0, s, Hkv, num_q_heads, T,
-                               scale_log2, oo, wm);
+            // (the grid is a multiple of the XCD count) A claim without its combine kernel
+            // would hold its slot for good.
+            const unsigned per_xcd = grid.x / kXcds;
+            hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+            hipError_t e = s ? hipStreamIsCapturing(s, &capture) : hipSuccess;   // (the null stream never is)
+            if (e != hipSuccess) return e;
+            e = enqueue(capture == hipStreamCaptureStatusNone ? split_claim_kernel : split_claim_replay_kernel,
+                        dim3(1), 64, s, wm.launch, per_xcd);
+            if (e != hipSuccess) return e;
+            e = enqueue(prefill_attn_kernel<D, kKeySplit>, grid, kThreads, s, qq, pk, pv, pool.num_blocks, Hkv,
+                        block_tables, max_blocks, num_q_heads, T, scale_log2, rescale_thr, oo, wm);
+            if (e == hipSuccess)
+                e = enqueue(split_combine_kernel<D>, grid, kCombineThreads, s, Hkv, num_q_heads, T, scale_log2, oo,
+                            wm);
+            if (e != hipSuccess) {
+                (void)enqueue(split_release_kernel, dim3(1), 64, s, wm.launch, per_xcd);
+                return e;
+            }
         }
+        return hipGetLastError();
     };
-    if (pool.head_dim == 128) launch(std::integral_constant<int, 128>{});
-    else launch(std::integral_constant<int, 64>{});
-    return hipGetLastError();
+    if (pool.head_dim == 128) return launch(std::integral_constant<int, 128>{});
+    return launch(std::integral_constant<int, 64>{});
 }
 }  // namespace
 
 void attn_set_schedule(int schedule) { g_schedule.store(schedule, std::memory_order_relaxed); }
+
+namespace {
+constexpr int kMaxDevices = 64;
+std::mutex g_hold_mu;
+uint64_t g_held[kMaxDevices][kSplitSlots];   // numbers under which attn_hold_scratch claimed; 0: none
+}  // namespace
+
+hipError_t attn_hold_scratch(int n, int *free_entries)
+{
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess && (dev < 0 || dev >= kMaxDevices)) e = hipErrorInvalidDevice;
+    if (e == hipSuccess) e = hipDeviceSynchronize();
+    if (e != hipSuccess) return e;
+    std::lock_guard<std::mutex> lk(g_hold_mu);
+    // Each slot is claimed twice under its number, as by two overlapping replays of one
+    // captured launch, and given back twice.
+    for (uint64_t &id : g_held[dev]) {
+        for (int k = 0; k < 2 && id && e == hipSuccess; ++k)
+            e = enqueue(split_release_kernel, dim3(1), 64, nullptr, id, 1u);
+        id = 0;
+    }
+    for (int i = 0; i < n && i < kSplitSlots && e == hipSuccess; ++i) {
+        g_held[dev][i] = next_launch();
+        for (int k = 0; k < 2 && e == hipSuccess; ++k)
+            e = enqueue(split_claim_replay_kernel, dim3(1), 64, nullptr, g_held[dev][i], 1u);
+    }
+    if (e == hipSuccess) e = hipDeviceSynchronize();
+    static SplitControl c;                   // (under the mutex)
+    if (e == hipSuccess) e = hipMemcpyFromSymbol(&c, HIP_SYMBOL(split_control), sizeof(c));
+    if (e != hipSuccess) return e;
+    *free_entries = 0;
+    for (int s = 0; s < kSplitEntries; ++s) {
+        bool through = true;
+        for (int x = 0; x < kXcds; ++x) through = through && (c.done[s][x][0] & 0xFFFFu) == (c.owner[s] & 0xFFFFu);
+        *free_entries += through;
+    }
+    return hipSuccess;
+}
 
 hipError_t launch_prefix_prefill_attn(const void *q, const pcr_kv_pool &pool,
                                       const int32_t *block_tables, int32_t max_blocks,
@@ -1391,7 +1533,7 @@ hipError_t launch_prefix_prefill_attn(const void *q, const pcr_kv_pool &pool,
     // that need no merge are written beside them: not for outputs that overlap q.
     const uintptr_t qa = (uintptr_t)q, oa = (uintptr_t)out;
     const uintptr_t bytes = (uintptr_t)T * num_q_heads * pool.head_dim * 2;
-    const bool can_split = n_launch == 1 && oa >> 48 == 0 && (qa + bytes <= oa || oa + bytes <= qa);
+    const bool can_split = n_launch == 1 && (qa + bytes <= oa || oa + bytes <= qa);
     for (int l = 0; l < n_launch; ++l) {
         int n = 0;
         for (int k = l; k < n_act; k += n_launch) group[n++] = seq[k];

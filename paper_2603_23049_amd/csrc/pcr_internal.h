@@ -117,6 +117,7 @@ pcr_status prefix_prefill_attn(const void *q, const pcr_kv_pool *pool, const int
 int attn_rows_per_workgroup(int head_dim);
 // Process-wide attention schedule (PCR_ATTN_SCHEDULE_*), read at each launch.
 void attn_set_schedule(int schedule);
+hipError_t attn_hold_scratch(int n, int *free_entries);
 
 // Every argument check of pcr_prefix_prefill_attn, with no launch (errors name `who`);
 // on success *T_out is the suffix token count (0: nothing to do).

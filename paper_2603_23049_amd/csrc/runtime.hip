@@ -692,6 +692,19 @@ pcr_status pcr_prefill_attn_set_schedule(int32_t schedule)
     return PCR_OK;
 }
 
+pcr_status pcr_prefill_attn_hold_scratch(int32_t n, int32_t *free_entries)
+{
+    g_err[0] = 0;
+    const char *who = "pcr_prefill_attn_hold_scratch";
+    if (n < 0 || n > 8) return fail(PCR_ERR_INVALID_ARG, "%s: n must be 0 to 8", who);
+    if (!free_entries) return fail(PCR_ERR_INVALID_ARG, "%s: free_entries is NULL", who);
+    int left = 0;
+    const hipError_t e = attn_hold_scratch(n, &left);
+    if (e != hipSuccess) return hip_fail(e, who);
+    *free_entries = left;
+    return PCR_OK;
+}
+
 pcr_status pcr_decode_attn_workspace_size(int32_t B, int32_t num_q_heads, int32_t num_kv_heads, int32_t head_dim,
                                           int32_t max_context, int64_t *bytes)
 {

@@ -183,6 +183,11 @@ def test_argument_validation_before_any_device_work():
     assert L.pcr_prefill_attn_set_schedule(-1) == pcr.PCR_ERR_INVALID_ARG
     for sch in (2, 1, 0):
         assert L.pcr_prefill_attn_set_schedule(sch) == pcr.PCR_OK
+    # scratch of key-split launches: 0 to 8 parts held
+    left = ctypes.c_int32(-1)
+    for n, to in ((-1, left), (9, left), (0, None)):
+        assert L.pcr_prefill_attn_hold_scratch(n, to and ctypes.byref(to)) == pcr.PCR_ERR_INVALID_ARG
+    assert left.value == -1
     # staged pipeline: streams, workspace and pool shapes are checked before anything is queued
     slot = 2 * 3 * 16 * 2 * 64 * 2        # 3 pairs of (16-token, 2-head, d=64) K and V blocks
     bat2.n_pairs = 3

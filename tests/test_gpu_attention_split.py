@@ -122,6 +122,34 @@ def test_split_launches_on_many_streams():
     assert torch.equal(L.out, eager)
 
 
+def test_overlapping_calls_with_one_output_keep_the_scratch_whole():
+    """Equal calls on several streams write one output: each has scratch of its own, the
+    bits are those of one call, and every part of the scratch is free afterwards. So do
+    replays of one captured call, which share theirs."""
+    L, _, _ = _layer([5000], [24], 4, 8, 128, seed=44)
+    say("[gpu] key split, one output on 6 streams")
+    L.attn()
+    torch.cuda.synchronize()
+    eager = L.out.clone()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        L.attn()
+    streams = [torch.cuda.Stream() for _ in range(6)]
+    for replay in (False, True):
+        for _ in range(5):
+            L.out.fill_(-1)
+            torch.cuda.synchronize()
+            for _ in range(4):
+                for s in streams:
+                    if replay:
+                        with torch.cuda.stream(s):
+                            g.replay()
+                    else:
+                        L.attn(stream=s)
+            torch.cuda.synchronize()
+            assert torch.equal(L.out, eager)
+
+
 def test_output_in_place_of_the_queries_is_not_split():
     """Chunks of one row tile read its queries after others have been written out, so an
     output that overlaps q takes the launch without chunks."""
