@@ -98,9 +98,8 @@ def test_split_launch_replayed_from_a_graph_beside_eager_calls():
 
 
 def test_split_launches_on_many_streams():
-    """More streams than the scratch holds launches: whichever launches overlap, every
-    output is right (one that finds the scratch taken runs without chunks), and the
-    scratch is whole again afterwards."""
+    """Claims and reuse of the scratch by launches that overlap (as many as the hardware
+    queues run at once): every output is right, and the scratch is whole again afterwards."""
     L, rows, want = _layer([5000], [24], 4, 8, 128, seed=43)
     say("[gpu] key split on 12 streams")
     L.attn()
@@ -120,6 +119,49 @@ def test_split_launches_on_many_streams():
     L.attn()
     torch.cuda.synchronize()
     assert torch.equal(L.out, eager)
+    assert pcr.prefill_attn_hold_scratch(0) == 64
+
+
+@pytest.mark.parametrize("pl,sl,G,Hkv,d", [([3000], [20], 4, 8, 128), ([2500], [70], 5, 3, 64), ([4000], [1], 4, 8, 128),
+                                           ([3000, 2000, 10], [1, 33, 1], 8, 2, 64)])
+def test_launch_that_finds_the_scratch_taken_runs_whole(pl, sl, G, Hkv, d):
+    """With every part of the scratch held, a call and a replay of a captured call take every
+    key in one piece (the bits of key halves, tile rows and one-token rows); with one part
+    free, and after all are, they cut the keys again."""
+    say(f"[gpu] key split, scratch held: p={pl} s={sl} G={G} Hkv={Hkv} d={d}")
+    L, rows, want = _layer(pl, sl, G, Hkv, d, seed=48 + G)
+
+    def both():
+        outs = []
+        for call in (L.attn, g.replay):
+            L.out.fill_(-1)
+            call()
+            torch.cuda.synchronize()
+            outs.append(L.out.clone())
+        assert torch.equal(*outs), "replay and call differ"
+        return outs[0]
+
+    with attn_schedule("key_halves"):
+        L.attn()
+    torch.cuda.synchronize()
+    whole = L.out.clone()
+    L.attn()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        L.attn()
+    cut = both()
+    assert not torch.equal(cut, whole)
+    try:
+        assert pcr.prefill_attn_hold_scratch(8) == 56
+        assert torch.equal(both(), whole)
+        assert torch.equal(both(), whole)
+        assert pcr.prefill_attn_hold_scratch(7) == 57
+        assert torch.equal(both(), cut)
+    finally:
+        free = pcr.prefill_attn_hold_scratch(0)
+    assert free == 64
+    assert torch.equal(both(), cut)
+    _check(L, rows, want, "cut")
 
 
 def test_overlapping_calls_with_one_output_keep_the_scratch_whole():
@@ -148,6 +190,7 @@ def test_overlapping_calls_with_one_output_keep_the_scratch_whole():
                         L.attn(stream=s)
             torch.cuda.synchronize()
             assert torch.equal(L.out, eager)
+    assert pcr.prefill_attn_hold_scratch(0) == 64
 
 
 def test_output_in_place_of_the_queries_is_not_split():
