@@ -177,7 +177,7 @@ def _stream(stream) -> Optional[int]:
 
 
 def _i32_host(a) -> np.ndarray:
-    if isinstance(a, np.ndarray) and a.dtype is _INT32 and a.flags.c_contiguous:
+    if type(a) is np.ndarray and a.dtype is _INT32 and a.ndim and a.flags.c_contiguous:
         return a
     return np.ascontiguousarray(np.asarray(a, dtype=np.int32))
 

@@ -96,3 +96,6 @@ def test_pointers_of_host_arrays():
         y = pcr._i32_host(x)
         assert y.dtype == np.int32 and y.flags.c_contiguous and y.dtype.isnative and list(y) == list(x)
     assert pcr._i32_host(a) is a and pcr._i32_host(ro) is ro
+    for x in (np.array(7, np.int32), np.ma.masked_array(a, a > 3)):     # one length; a subclass
+        y = pcr._i32_host(x)
+        assert type(y) is np.ndarray and y.ndim == 1 and y.tolist() == np.asarray(x).reshape(-1).tolist()
