@@ -99,3 +99,17 @@ def test_pointers_of_host_arrays():
     for x in (np.array(7, np.int32), np.ma.masked_array(a, a > 3)):     # one length; a subclass
         y = pcr._i32_host(x)
         assert type(y) is np.ndarray and y.ndim == 1 and y.tolist() == np.asarray(x).reshape(-1).tolist()
+
+
+def test_current_stream_without_the_raw_handle(monkeypatch):
+    """On a torch that lacks the raw-handle calls, the stream comes from the public one."""
+    import torch
+
+    class Stream:
+        cuda_stream = 77
+
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", Stream)
+    for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"):
+        monkeypatch.delattr(torch._C, name, raising=False)
+    assert pcr._stream(None) == 77
