@@ -28,6 +28,7 @@
 // decode_combine_kernel merges the chunks of each (sequence, head).
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "decode_wave.h"
 #include "pcr_internal.h"
@@ -64,7 +65,11 @@ constexpr int kMinChunk = 256;         // keys; shorter chunks spend more on set
 constexpr int kMaxSub = kWaves;
 constexpr float kLog2e = 1.4426950408889634f;
 
-template <int D, bool K_CACHED>
+// SHARED: a workgroup's waves share one chunk, part_keys of it each, and merge in LDS;
+// otherwise each wave takes a chunk (all n_split of one sequence when those merge in LDS).
+// A template parameter, since telling the two apart in the kernel cost every chunk 0.3 us
+// (12 contexts of 1k-8k); part_keys comes from the host, so that no wave divides for it.
+template <int D, bool K_CACHED, bool SHARED>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1))) void decode_split_kernel(
     const u16 *__restrict__ q, const u16 *__restrict__ pool_k, const u16 *__restrict__ pool_v,
     int32_t num_blocks, int32_t Hkv, const int32_t *__restrict__ block_tables, int32_t max_blocks,
@@ -75,12 +80,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1))) v
     constexpr int MT = D / 16;    // V products (16 dims each)
     const int lane = (int)(threadIdx.x & 63);
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    // A workgroup whose waves share one chunk (part_keys of it each) merges in LDS; otherwise
-    // each wave takes a chunk (all n_split of one sequence when those merge in LDS).
-    // part_keys comes from the host, so that no wave divides for it.
-    const bool shared = part_keys < chunk;
     const int wg_waves = (int)(blockDim.x >> 6);
-    const int64_t task = shared ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * wg_waves + wave;
+    const int64_t task = SHARED ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * wg_waves + wave;
     if (task >= (int64_t)B * Hkv * n_split) return;   // never for a merging workgroup (exact grid)
     const int sp = (int)(task % n_split);
     const int bg = (int)(task / n_split);
@@ -88,8 +89,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1))) v
     const int n_keys = context_lens[b];
     const int c0 = sp * chunk, c1 = min(n_keys, c0 + chunk);   // the chunk's keys
     if (c0 >= n_keys && !lds_merge) return;        // (a wave of a sequence that merges in LDS stays for the barrier)
-    const int kbeg = c0 + (shared ? wave * part_keys : 0);
-    const int kend = min(c1, kbeg + part_keys);
+    const int kbeg = c0 + (SHARED ? wave * part_keys : 0);
+    const int kend = SHARED ? min(c1, kbeg + part_keys) : c1;
     const bool active = kbeg < c1;                 // wave-uniform
     const int last_blk = max(0, min((n_keys - 1) >> 4, max_blocks - 1));   // last block with a visible key
     const int G = Hq / Hkv;
@@ -110,7 +111,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1))) v
 
     float l_tot = l_run + __shfl_xor(l_run, 16);
     l_tot += __shfl_xor(l_tot, 32);
-    if (lds_merge || shared) {
+    if (lds_merge || SHARED) {
         // The workgroup holds every chunk of one (sequence, kv head), or every part of one
         // chunk. Waves 1.. leave their O (lane layout), max and sum in LDS; wave 0 merges and
         // writes. A part past the end, or without a finite score, contributes max kNoMax,
@@ -376,11 +377,15 @@ hipError_t launch_decode_attn(const void *q, const pcr_kv_pool &pool, const int3
                            max_blocks, context_lens, B, num_q_heads, plan.n_split, plan.chunk, scale_log2, lds_merge,
                            part_keys, oo, ws_o, ws_ml);
     };
-    if (D == 128) {
-        if (plan.k_streamed) split(decode_split_kernel<128, false>); else split(decode_split_kernel<128, true>);
-    } else {
-        if (plan.k_streamed) split(decode_split_kernel<64, false>); else split(decode_split_kernel<64, true>);
-    }
+    // (a batch that shares chunks leaves SIMDs idle, so it never streams K)
+    auto split_d = [&](auto dim) {
+        constexpr int DD = decltype(dim)::value;
+        if (sub > 1) split(decode_split_kernel<DD, true, true>);
+        else if (plan.k_streamed) split(decode_split_kernel<DD, false, false>);
+        else split(decode_split_kernel<DD, true, false>);
+    };
+    if (D == 128) split_d(std::integral_constant<int, 128>{});
+    else split_d(std::integral_constant<int, 64>{});
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !through_ws) return e;
     const dim3 cgrid((unsigned)(((int64_t)B * num_q_heads + kWaves - 1) / kWaves));
