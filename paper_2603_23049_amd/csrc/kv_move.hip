@@ -24,6 +24,8 @@ constexpr int kGatherTile = 32;
 // and 3-15% of a gather of 163-268 MB. Below it inputs of a producer kernel are still
 // cached, and non-temporal loads cost 12-20% (appends of 14-33 MB).
 constexpr int64_t kNtBytes = 64ll << 20;
+// Output bytes up to which gather runs one thread per 16 bytes of a row (gather_rows_kernel).
+constexpr int64_t kGatherRowsBytes = 4ll << 20;
 // New tokens per append workgroup: 32 measured as fast as 16 on block-aligned slot lists
 // and 31% faster on the RAG mix's (whose tiles start inside chunks); 64 was 3.5% slower
 // on aligned lists of 128k tokens.
@@ -208,6 +210,9 @@ __global__ __launch_bounds__(256) void gather_kv_kernel(
 
     const int g = blockIdx.y, tid = threadIdx.x;
     const int row0 = blockIdx.x * TILE;
+    auto put = [&](u16 *dst, u32x4 v) __attribute__((always_inline)) {
+        __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(dst));
+    };
     if (tid < 64) {                            // wave 0: where each row lies, and the chunk runs
         const int r = row0 + tid;
         int32_t blk = -1, o = 0;
@@ -285,10 +290,50 @@ __global__ __launch_bounds__(256) void gather_kv_kernel(
             const int64_t dst = ((int64_t)(row0 + r) * Hkv + g) * D + cc * 8;
             u32x4 vv = {0u, 0u, 0u, 0u};
             if (blks[r] >= 0) vv = *reinterpret_cast<const u32x4 *>(&vs[r][cc * 8]);
-            __builtin_nontemporal_store(kv[i], reinterpret_cast<u32x4 *>(k_out + dst));
-            __builtin_nontemporal_store(vv, reinterpret_cast<u32x4 *>(v_out + dst));
+            put(k_out + dst, kv[i]);
+            put(v_out + dst, vv);
         }
     }
+}
+
+// The same for calls of few rows, which wait on latency: one thread per 16 bytes of K and V
+// finds its row by itself, and takes V in eight 2-byte loads, all in flight with K's. No
+// barrier, and no serial tasks where every row is a sequence of its own (64 one-token
+// sequences of 8 kv heads of 128: 4.8 us here, 7.7 in tiles; 64 tokens of one 3.9 and 4.5; 600
+// 5.4 and 5.0, 2048, above the line, 9.5 and 7.5; one kv head 4096 4.6 and 5.5, 8192 5.6 and 6.1).
+template <int D>
+__global__ __launch_bounds__(256) void gather_rows_kernel(
+    const u16 *__restrict__ pool_k, const u16 *__restrict__ pool_v, int32_t num_blocks, int32_t Hkv,
+    const int32_t *__restrict__ block_tables, int32_t max_blocks,
+    const int32_t *__restrict__ starts, const int32_t *__restrict__ cu_out, int32_t B,
+    int32_t total, u16 *__restrict__ k_out, u16 *__restrict__ v_out)
+{
+    constexpr int CPR = D / 8;                 // 16-B chunks per row
+    const int g = blockIdx.y, r = blockIdx.x * (256 / CPR) + threadIdx.x / CPR, c = threadIdx.x % CPR;
+    if (r >= total) return;
+    int lo = 0, hi = B - 1;                    // sequence with cu_out[lo] <= r < cu_out[lo + 1]
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) / 2;
+        if (cu_out[mid] <= r) lo = mid; else hi = mid - 1;
+    }
+    const int t = starts[lo] + (r - cu_out[lo]), o = t % kBlockSize;
+    u32x4 kw = {0u, 0u, 0u, 0u}, vw = {0u, 0u, 0u, 0u};
+    if (t >= 0 && t / kBlockSize < max_blocks) {
+        const int32_t blk = block_tables[(int64_t)lo * max_blocks + t / kBlockSize];
+        if (blk >= 0 && blk < num_blocks) {
+            const int64_t payload = ((int64_t)blk * Hkv + g) * kBlockSize * D;
+            kw = *reinterpret_cast<const u32x4 *>(pool_k + payload + o * D + c * 8);
+            const u16 *vp = pool_v + payload + c * 8 * kBlockSize + o;
+            u16 e[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) e[k] = vp[k * kBlockSize];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) vw[k] = e[2 * k] | ((unsigned)e[2 * k + 1] << 16);
+        }
+    }
+    const int64_t dst = ((int64_t)r * Hkv + g) * D + c * 8;
+    *reinterpret_cast<u32x4 *>(k_out + dst) = kw;
+    *reinterpret_cast<u32x4 *>(v_out + dst) = vw;
 }
 
 // ---------------------------------------------------------------------------
@@ -369,20 +414,22 @@ hipError_t launch_gather_kv(const pcr_kv_pool &pool, const int32_t *block_tables
                             const int32_t *starts, const int32_t *cu_out, int32_t B, int32_t total,
                             void *k_out, void *v_out, hipStream_t s)
 {
-    const dim3 grid((total + kGatherTile - 1) / kGatherTile, pool.num_kv_heads);
-    auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, static_cast<const u16 *>(pool.k),
-                           static_cast<const u16 *>(pool.v), pool.num_blocks, pool.num_kv_heads, block_tables,
-                           max_blocks, starts, cu_out, B, total, static_cast<u16 *>(k_out), static_cast<u16 *>(v_out));
+    const int D = pool.head_dim, Hkv = pool.num_kv_heads;
+    const int64_t out_bytes = 2 * (int64_t)total * Hkv * D * 2;
+    auto launch = [&](auto kernel, int tile) {
+        hipLaunchKernelGGL(kernel, dim3((total + tile - 1) / tile, Hkv), dim3(256), 0, s,
+                           static_cast<const u16 *>(pool.k), static_cast<const u16 *>(pool.v), pool.num_blocks, Hkv,
+                           block_tables, max_blocks, starts, cu_out, B, total, static_cast<u16 *>(k_out),
+                           static_cast<u16 *>(v_out));
     };
-    const bool nt = 2 * (int64_t)total * pool.num_kv_heads * pool.head_dim * 2 >= kNtBytes;
-    if (pool.head_dim == 128) {
-        if (nt) launch(gather_kv_kernel<128, kGatherTile, true>);
-        else launch(gather_kv_kernel<128, kGatherTile, false>);
-    } else {
-        if (nt) launch(gather_kv_kernel<64, kGatherTile, true>);
-        else launch(gather_kv_kernel<64, kGatherTile, false>);
-    }
+    auto launch_d = [&](auto dim) {
+        constexpr int DD = decltype(dim)::value;
+        if (out_bytes <= kGatherRowsBytes) launch(gather_rows_kernel<DD>, 256 / (DD / 8));
+        else if (out_bytes >= kNtBytes) launch(gather_kv_kernel<DD, kGatherTile, true>, kGatherTile);
+        else launch(gather_kv_kernel<DD, kGatherTile, false>, kGatherTile);
+    };
+    if (D == 128) launch_d(std::integral_constant<int, 128>{});
+    else launch_d(std::integral_constant<int, 64>{});
     return hipGetLastError();
 }
 

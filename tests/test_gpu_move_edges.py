@@ -65,6 +65,22 @@ def test_gather_edges(d, Hkv):
     _gather_case([-5, 3], [20, 40], Hkv, d, 32)    # a start before the sequence: zero rows
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Hkv", [1, 3, 8])
+def test_gather_edges_in_tiles(d, Hkv):
+    """The edges above in calls of more than 4 MiB of output, which tiles of 32 rows take (and
+    the last call that goes row by row); a first sequence shifts them against the tiles."""
+    most = (4 << 20) // (4 * Hkv * d)                  # rows of the last call that goes row by row
+    say(f"[gpu] gather edges in tiles d={d} Hkv={Hkv}, from {most + 1} rows on")
+    _gather_case([3], [most], Hkv, d, 40)
+    _gather_case([3], [most + 1], Hkv, d, 41)
+    small = [1, 31, 33, 64, 65, 96, 7, 0, 17, 1, 0, 33, 8, 9] + [1, 2, 3, 5, 7, 9, 0] * 10
+    starts = [7, 1, 8, 15, 16, 5, 31, 3, 0, 40, 9, 0, 15, 2] + list(range(70))
+    for shift in (0, 1, 15, 30):
+        _gather_case([9] + starts, [most + shift] + small, Hkv, d, 50 + shift, missing=20)
+    _gather_case([-5, 3], [most, 40], Hkv, d, 60)      # a start before the sequence: zero rows
+
+
 def test_gather_large_with_nontemporal_loads():
     rng = np.random.Generator(np.random.PCG64(5))
     lens = [int(x) for x in rng.integers(900, 1200, size=17)]
