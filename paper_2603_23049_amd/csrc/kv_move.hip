@@ -18,11 +18,13 @@ typedef unsigned short u16;
 // Output rows per gather workgroup: 16 and 64 were 2-5% slower on 268 MB, 16 20% on two
 // kv heads.
 constexpr int kGatherTile = 32;
-// Input bytes from which append and gather read with non-temporal loads: what a call
-// this large reads has left the caches (32 MB of L2; the 256 MB behind it hold the
-// writes too), and passing them by saved 11% of a 151 MB ragged append (35.8 -> 31.9 us)
-// and 3-15% of a gather of 163-268 MB. Below it inputs of a producer kernel are still
-// cached, and non-temporal loads cost 12-20% (appends of 14-33 MB).
+// Bytes of input (append) or output (gather) from which both go past the caches: non-
+// temporal loads and, for gather, stores. Appends of 16k, 20k and 32k tokens of 8 kv heads
+// of 128 (4 KB a token), ordinary -> non-temporal loads: 40 -> 31, 49 -> 39 and 72 -> 61 us
+// when the input has left the caches; 25 -> 28, 31 -> 35 and 49 -> 54 in ragged sequences,
+// 22 -> 22, 27 -> 27 and 45 -> 49 in aligned ones, when the layer's passes have just written
+// it (28, 34, 54 and 22, 27, 44 with tiles cut at token 32). Smaller inputs are cached more
+// often, and lose 12-20% (14-33 MB).
 constexpr int64_t kNtBytes = 64ll << 20;
 // Output bytes up to which gather runs one thread per 16 bytes of a row (gather_rows_kernel).
 constexpr int64_t kGatherRowsBytes = 4ll << 20;
@@ -183,13 +185,16 @@ __global__ __launch_bounds__(256) void append_kv_kernel(
 // workgroup reads TILE output rows of one kv head. K rows are copied 16 B at a time.
 // V is d-major inside a block: each aligned chunk of 8 slots of one dim that the tile's
 // rows use is read by one 16-byte load (two dims per task), its elements go through LDS,
-// and the rows leave it 16 B at a time, with non-temporal stores (whole lines that
-// this kernel does not read again). Bound by moving the bytes: 19897 ragged tokens
+// and the rows leave it 16 B at a time. Bound by moving the bytes: 19897 ragged tokens
 // (163 MB) 58.5 us when V was read by eight 2-byte loads per 16 bytes of output, 39 with
-// whole chunks, 31.4 with the non-temporal stores, 30.5 = 5.3 TB/s with the K loads
+// whole chunks, 31.4 with non-temporal stores, 30.5 = 5.3 TB/s with the K loads
 // non-temporal too (NT; V loads stay ordinary: a line's two 16-byte halves are read by
 // different tasks, and bypassing the caches took 41 us); 268 MB of aligned tokens
-// 99.5 -> 45 us = 5.9 TB/s.
+// 99.5 -> 45 us = 5.9 TB/s. Output that passes the caches by costs its reader: gather and a
+// kernel that reads its output together, with input out of the caches, took 42 us for 8192
+// tokens of 8 kv heads of 128 by 2-byte loads, 43 with non-temporal stores, 38 without;
+// 16384 (67 MB out) 82, 73, 68, 65536 308, 224, 222; with cached input 16384 65, 48, 48, 32768
+// 151, 93, 103. So they start at kNtBytes.
 // A row whose block is not in the pool or past the table is written as zeros.
 // ---------------------------------------------------------------------------
 template <int D, int TILE, bool NT>
@@ -211,7 +216,8 @@ __global__ __launch_bounds__(256) void gather_kv_kernel(
     const int g = blockIdx.y, tid = threadIdx.x;
     const int row0 = blockIdx.x * TILE;
     auto put = [&](u16 *dst, u32x4 v) __attribute__((always_inline)) {
-        __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(dst));
+        if constexpr (NT) __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(dst));
+        else *reinterpret_cast<u32x4 *>(dst) = v;
     };
     if (tid < 64) {                            // wave 0: where each row lies, and the chunk runs
         const int r = row0 + tid;
