@@ -28,6 +28,9 @@ constexpr int kGatherTile = 32;
 constexpr int64_t kNtBytes = 64ll << 20;
 // Output bytes up to which gather runs one thread per 16 bytes of a row (gather_rows_kernel).
 constexpr int64_t kGatherRowsBytes = 4ll << 20;
+// Append workgroups up to which each requests the rows it may take after its tile with the
+// tile's own rows (append_kv_kernel).
+constexpr int kAppendEarly = 256;
 // New tokens per append workgroup: 32 measured as fast as 16 on block-aligned slot lists
 // and 31% faster on the RAG mix's (whose tiles start inside chunks); 64 was 3.5% slower
 // on aligned lists of 128k tokens.
@@ -50,8 +53,13 @@ constexpr int kAppendTile = 32;
 // NT: the input rows are read with non-temporal loads. (The pool is written with
 // ordinary stores, which merge a block's 16-byte chunks into lines in the L2:
 // non-temporal ones took 1.5 to 2 times as long.)
+// EARLY: the rows after the tile are requested with the tile's, before the slots say whether
+// they are this tile's, since a second round trip to memory is what a small call waits for
+// (64 tokens of 8 kv heads 4.6 -> 4.2 us, of 64 dims 4.0 -> 3.6; 1024 ragged ones 5.3 -> 5.0). With more
+// workgroups than compute units the extra reads cost more (4096 ragged tokens of 64 dims
+// 6.1 -> 6.6).
 // ---------------------------------------------------------------------------
-template <int D, int TILE, bool NT>
+template <int D, int TILE, bool NT, bool EARLY>
 __global__ __launch_bounds__(256) void append_kv_kernel(
     u16 *__restrict__ pool_k, u16 *__restrict__ pool_v, int32_t num_blocks, int32_t Hkv,
     const u16 *__restrict__ k_new, const u16 *__restrict__ v_new,
@@ -91,10 +99,21 @@ __global__ __launch_bounds__(256) void append_kv_kernel(
             vv[i] = load(v_new + src);
         }
     }
-    if (tid < 64) {                            // wave 0: the slots, and the chunk runs
+    u32x4 ke = {0u, 0u, 0u, 0u}, ve = {0u, 0u, 0u, 0u};
+    const int re = TILE + tid / CPR, ce = tid % CPR;   // this thread's chunk of the rows after the tile
+    auto load_ext = [&]() __attribute__((always_inline)) {
+        const int64_t src = ((int64_t)(tok0 + re) * Hkv + g) * D + ce * 8;
+        ke = load(k_new + src);
+        ve = load(v_new + src);
+    };
+    if constexpr (EARLY) {
+        if (re < ROWS && tok0 + re < T) load_ext();
+    }
+    int32_t sl = -1;                           // wave 0: the slot of token tok0 + tid
+    bool follows = false;                      // and whether it follows the token before's
+    if (tid < 64) {
         // Lane 63 reads the slot of the token before the tile (all slots in one load).
         const int t = tid == 63 ? tok0 - 1 : tok0 + tid;
-        int32_t sl = -1;
         if ((tid < ROWS || tid == 63) && t >= 0 && t < T) {
             sl = slot_mapping[t];
             if (sl < 0 || sl / kBlockSize >= num_blocks) sl = -1;
@@ -102,7 +121,7 @@ __global__ __launch_bounds__(256) void append_kv_kernel(
         // the slot of the token before this one (the wave rotated by one lane: DPP wave_ror:1)
         const int32_t before = __builtin_amdgcn_update_dpp(sl, sl, 0x13C, 0xf, 0xf, false);
         if (tid == 63) sl = -1;
-        const bool follows = sl >= 0 && before >= 0 && sl == before + 1;
+        follows = sl >= 0 && before >= 0 && sl == before + 1;
         // heads: tokens that do not go on inside the block of the token before them. The
         // tile's own tokens run from its first head to the first head at or after its end
         // (both within 15 tokens: a block has 16 slots).
@@ -111,6 +130,23 @@ __global__ __launch_bounds__(256) void append_kv_kernel(
         const int first = (int)__builtin_ctzll(heads);
         const int last = rest ? min(ROWS, TILE + (int)__builtin_ctzll(rest)) : ROWS;
         if (tid < first || tid >= last) sl = -1;
+        if (tid < ROWS) slots[tid] = sl;
+        if (tid == 0) n_rows = last;
+    }
+    __syncthreads();
+
+    auto put_row = [&](int r, int cc, u32x4 kw, u32x4 vw) __attribute__((always_inline)) {
+        const int32_t s0 = slots[r];
+        if (s0 < 0) return;
+        *reinterpret_cast<u32x4 *>(&vs[r][cc * 8]) = vw;
+        const int64_t blk = s0 / kBlockSize, o = s0 % kBlockSize;
+        *reinterpret_cast<u32x4 *>(pool_k + ((blk * Hkv + g) * kBlockSize + o) * D + cc * 8) = kw;
+    };
+    const bool ext = re < n_rows;
+    if constexpr (!EARLY) {
+        if (ext) load_ext();
+    }
+    if (tid < 64) {                            // wave 0: the chunk runs
         // A token starts a chunk run when its slot is valid and either opens an aligned chunk
         // of 8 slots or does not follow the previous token's slot; the run goes on over the
         // following tokens until the next start or invalid slot (a continuing token's slot
@@ -125,28 +161,7 @@ __global__ __launch_bounds__(256) void append_kv_kernel(
             const int idx = __builtin_popcountll(starts & ((1ull << tid) - 1ull));
             runs[idx] = (tid << 8) | len;
         }
-        if (tid == 0) {
-            n_runs = __builtin_popcountll(starts);
-            n_rows = last;
-        }
-        if (tid < ROWS) slots[tid] = sl;
-    }
-    __syncthreads();
-
-    auto put_row = [&](int r, int cc, u32x4 kw, u32x4 vw) __attribute__((always_inline)) {
-        const int32_t sl = slots[r];
-        if (sl < 0) return;
-        *reinterpret_cast<u32x4 *>(&vs[r][cc * 8]) = vw;
-        const int64_t blk = sl / kBlockSize, o = sl % kBlockSize;
-        *reinterpret_cast<u32x4 *>(pool_k + ((blk * Hkv + g) * kBlockSize + o) * D + cc * 8) = kw;
-    };
-    u32x4 ke = {0u, 0u, 0u, 0u}, ve = {0u, 0u, 0u, 0u};
-    const int re = TILE + tid / CPR, ce = tid % CPR;   // this thread's chunk of the rows after the tile
-    const bool ext = re < n_rows;
-    if (ext) {
-        const int64_t src = ((int64_t)(tok0 + re) * Hkv + g) * D + ce * 8;
-        ke = load(k_new + src);
-        ve = load(v_new + src);
+        if (tid == 0) n_runs = __builtin_popcountll(starts);
     }
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
@@ -405,14 +420,14 @@ hipError_t launch_append_kv(const pcr_kv_pool &pool, const void *k_new, const vo
                            slot_mapping, T);
     };
     const int64_t in_bytes = 2 * (int64_t)T * pool.num_kv_heads * pool.head_dim * 2;
-    const bool nt = in_bytes >= kNtBytes;
-    if (pool.head_dim == 128) {
-        if (nt) launch(append_kv_kernel<128, kAppendTile, true>);
-        else launch(append_kv_kernel<128, kAppendTile, false>);
-    } else {
-        if (nt) launch(append_kv_kernel<64, kAppendTile, true>);
-        else launch(append_kv_kernel<64, kAppendTile, false>);
-    }
+    auto launch_d = [&](auto dim) {
+        constexpr int D = decltype(dim)::value;
+        if (in_bytes >= kNtBytes) launch(append_kv_kernel<D, kAppendTile, true, false>);
+        else if ((int64_t)grid.x * grid.y <= kAppendEarly) launch(append_kv_kernel<D, kAppendTile, false, true>);
+        else launch(append_kv_kernel<D, kAppendTile, false, false>);
+    };
+    if (pool.head_dim == 128) launch_d(std::integral_constant<int, 128>{});
+    else launch_d(std::integral_constant<int, 64>{});
     return hipGetLastError();
 }
 

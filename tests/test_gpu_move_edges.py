@@ -136,6 +136,26 @@ def test_append_edges(d, Hkv):
     _append_case(rng.permutation(400 * BS)[:777], 400, Hkv, d, 10)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Hkv", [1, 3, 8])
+def test_append_edges_of_many_workgroups(d, Hkv):
+    """From 257 workgroups on a tile asks for the rows after it only once it knows its slots;
+    the last call below does so at once."""
+    rng = np.random.Generator(np.random.PCG64(20 + d + Hkv))
+    most = 256 // Hkv * 32                             # tokens of 256 workgroups
+    nb = 4 * (most // 16)
+    seg = _segments(rng, nb // 4, nb)[:most + 40]
+    assert len(seg) == most + 40
+    say(f"[gpu] append edges of many workgroups d={d} Hkv={Hkv}: {len(seg)} tokens")
+    _append_case(seg[:most], nb, Hkv, d, 21)
+    _append_case(seg, nb, Hkv, d, 22)
+    _append_case(range(5, 5 + most + 33), nb, Hkv, d, 23)
+    holes = np.asarray(seg)
+    holes[rng.integers(0, len(seg), size=90)] = rng.choice([-1, nb * BS, 2**31 - 1], size=90)
+    _append_case(holes, nb, Hkv, d, 24)
+    _append_case(seg[::-1], nb, Hkv, d, 25)
+
+
 def test_append_large_ragged_with_nontemporal_loads():
     rng = np.random.Generator(np.random.PCG64(11))
     nb = 4 * 800
