@@ -81,13 +81,14 @@ def test_gather_edges_in_tiles(d, Hkv):
     _gather_case([-5, 3], [most, 40], Hkv, d, 60)      # a start before the sequence: zero rows
 
 
-def test_gather_large_with_nontemporal_loads():
+@pytest.mark.parametrize("Hkv,d", [(8, 128), (15, 64)])
+def test_gather_large_with_nontemporal_loads(Hkv, d):
     rng = np.random.Generator(np.random.PCG64(5))
-    lens = [int(x) for x in rng.integers(900, 1200, size=17)]
-    starts = [int(x) for x in rng.integers(0, 50, size=17)]
-    assert sum(lens) * 8 * 128 * 4 > 64 << 20
-    say(f"[gpu] gather large: {sum(lens)} tokens")
-    _gather_case(starts, lens, 8, 128, 6, missing=3)
+    lens = [int(x) for x in rng.integers(900, 1200, size=18)]
+    starts = [int(x) for x in rng.integers(0, 50, size=18)]
+    assert sum(lens) * Hkv * d * 4 > 64 << 20
+    say(f"[gpu] gather large: {sum(lens)} tokens, Hkv={Hkv} d={d}")
+    _gather_case(starts, lens, Hkv, d, 6, missing=3)
 
 
 def _append_case(slots, nb, Hkv, d, seed):
@@ -156,10 +157,11 @@ def test_append_edges_of_many_workgroups(d, Hkv):
     _append_case(seg[::-1], nb, Hkv, d, 25)
 
 
-def test_append_large_ragged_with_nontemporal_loads():
+@pytest.mark.parametrize("Hkv,d", [(8, 128), (15, 64)])
+def test_append_large_ragged_with_nontemporal_loads(Hkv, d):
     rng = np.random.Generator(np.random.PCG64(11))
     nb = 4 * 800
     seg = _segments(rng, 790, nb)
-    assert len(seg) * 8 * 128 * 4 > 64 << 20
-    say(f"[gpu] append large ragged: {len(seg)} tokens")
-    _append_case(seg, nb, 8, 128, 12)
+    assert len(seg) * Hkv * d * 4 > 64 << 20
+    say(f"[gpu] append large ragged: {len(seg)} tokens, Hkv={Hkv} d={d}")
+    _append_case(seg, nb, Hkv, d, 12)
