@@ -264,13 +264,14 @@ pcr_status pcr_prefix_prefill_attn(const void *q, const pcr_kv_pool *pool,
  * pcr_prefill_attn_set_schedule -- how pcr_prefix_prefill_attn (and the pipelines'
  * attention) divides a launch among workgroups; a tuning and testing control, not
  * part of the method. Every schedule computes the same result (Sec. 2.2).
- *   PCR_ATTN_SCHEDULE_AUTO (the default): of the two below the one estimated to take
- *     less time when there are more workgroups than compute units, else key halves, for
- *     launches that leave compute units idle with the keys cut into chunks; pcr_pipeline_run and
- *     pcr_pipeline_run_offload, whose pull-kernel loads share the compute units
- *     with the attention, take key halves unless the row-halves workgroups all fit the
- *     compute units at once (shorter workgroups let the copy workgroups onto a compute
- *     unit sooner), and never cut the keys;
+ *   PCR_ATTN_SCHEDULE_AUTO (the default): row halves from two of their workgroups per
+ *     compute unit on, below it key halves, unless the other of the two is estimated to take
+ *     4% less time; launches that leave compute units idle take key halves with the keys
+ *     cut into chunks. pcr_pipeline_run and pcr_pipeline_run_offload, whose pull-kernel
+ *     loads share the compute units with the attention, take key halves unless row halves
+ *     are estimated so and their workgroups all fit the compute units at once (shorter
+ *     workgroups let the copy workgroups onto a compute unit sooner), and never cut the
+ *     keys;
  *   PCR_ATTN_SCHEDULE_KEY_HALVES: 128 packed query rows per workgroup, the two
  *     wave groups on the two halves of the key range, merged at the end;
  *   PCR_ATTN_SCHEDULE_ROW_HALVES: 256 packed query rows per workgroup, each wave

@@ -1299,42 +1299,77 @@ int32_t split_chunk(const int32_t *seq, int n, const int32_t *host_prefix_lens, 
 }
 
 // Estimated time in us of a launch on row tiles of rpw rows (128: key halves, 256: row
-// halves): an item takes its fixed part plus its key tiles, whole rounds of n_cu items take
-// the mean item each, and a last round of few items runs faster, at the clock that the
-// idle compute units' power allows (42% of a full round's time and 57% in proportion to
-// its items). Measured with 128 dims (64 dims): 0.84 (0.57) us a key tile and 7 us with key
-// halves, 1.58 (1.2) and 8 with row halves, where one copy of a tile serves twice the
-// rows; 0.7 (0.35) us per 64 keys and 5 for a decode row. The estimates were within 8% of
-// 40 measured launches of 1 to 4 rounds, apart from short ones without a prefix.
-double schedule_time(const int32_t *seq, int n, const int32_t *host_prefix_lens, const int32_t *host_cu_suffix, int G,
-                     int Hkv, int D, int rpw, int n_cu)
+// halves) over the sequences in launch order. An item takes a fixed part plus its key
+// tiles: with 128 dims (64 dims) 7.3 (5.6) us and 0.79 (0.57) a tile with key halves, 10 (7.6)
+// and 1.45 (0.99) with row halves, where one copy of a tile serves twice the rows; a
+// decode row 5 (3.6) and 0.98 (0.45) per 64 keys. With `simulate` (at most kSimItems items) each
+// XCD's items are dealt in launch order to whichever of its compute units is free first,
+// as the hardware does: sequences of short prefixes have items of 2 to 30 tiles, and the
+// mean of them says little about the last to end. While compute units idle the others
+// run at a higher clock (the power they leave): idle time counts 70% (88%). Without
+// `simulate`: the work over the compute units, for launches of many rounds.
+// Measured on 440 launches of 1 to 9 rounds (8 to 96 query / 1 to 8 kv heads, ragged and not,
+// decode rows among them): the choice below loses 0.4% against always the faster one and
+// 1.2% at worst against the line of two row-halves items per compute unit, which itself loses 3.7%;
+// an estimate from the items' mean lost up to 11% against that line in 29 of them, and
+// 30% on two sequences of 2100 new tokens on 90 cached with 28 / 4 heads (103 -> 79 us).
+constexpr int kSimItems = 1024;
+double schedule_time(const int32_t *order, int n, const int32_t *host_prefix_lens, const int32_t *host_cu_suffix,
+                     int G, int Hkv, int D, int rpw, int n_cu, bool simulate)
 {
-    const bool rows = rpw > kRowsPerWG;
-    const double fixed = rows ? 8.0 : 7.0, dec_tile = 0.7 * D / 128;
-    const double tile = D == 128 ? (rows ? 1.58 : 0.84) : (rows ? 1.2 : 0.57);
-    double total = 0.0, longest = 0.0;
-    int64_t items = 0;
+    const bool rows = rpw > kRowsPerWG, wide = D == 128;
+    const float fixed = rows ? (wide ? 10.f : 7.6f) : (wide ? 7.3f : 5.6f);
+    const float tile = rows ? (wide ? 1.45f : 0.99f) : (wide ? 0.79f : 0.57f);
+    const float dec_fixed = wide ? 5.f : 3.6f, dec_tile = wide ? 0.98f : 0.45f;
+    float cost[kSimItems];                   // one kv head's items
+    int items = 0;
+    double total = 0.0;
     for (int k = 0; k < n; ++k) {
-        const int32_t b = seq[k], p = host_prefix_lens[b], sb = host_cu_suffix[b + 1] - host_cu_suffix[b];
-        const int last = key_tiles(p + sb - 1);
+        const int32_t b = order[k], p = host_prefix_lens[b], sb = host_cu_suffix[b + 1] - host_cu_suffix[b];
         if (sb == 1 && G <= decode_wave::kMaxCols) {
-            const double t = 5.0 + dec_tile * last;
+            const float t = dec_fixed + dec_tile * key_tiles(p);
             total += t;
-            longest = std::max(longest, t);
-            ++items;
-        } else {
-            const int64_t r = (int64_t)sb * G, nt = (r + rpw - 1) / rpw;
-            const int first = key_tiles(p + (int)((std::min<int64_t>(r, rpw) - 1) / G));
+            if (simulate) cost[items++] = t;
+            continue;
+        }
+        const int64_t r = (int64_t)sb * G, nt = (r + rpw - 1) / rpw;
+        if (!simulate) {
+            const int first = key_tiles(p + (int)((std::min<int64_t>(r, rpw) - 1) / G)), last = key_tiles(p + sb - 1);
             total += nt * (fixed + tile * 0.5 * (first + last));
-            longest = std::max(longest, fixed + tile * last);
-            items += nt;
+            continue;
+        }
+        for (int64_t t = nt - 1; t >= 0; --t) {
+            cost[items++] = fixed + tile * key_tiles(p + (int)((std::min<int64_t>(r, (t + 1) * rpw) - 1) / G));
         }
     }
-    const double mean = total / items;
-    items *= Hkv;
-    const int64_t rounds = items / n_cu, over = items % n_cu;
-    const double part = 0.42 + 0.57 * over / n_cu;
-    return std::max(rounds * mean + (over ? part * mean : 0.0), longest * (rounds ? 1.0 : part));
+    if (!simulate) return total * Hkv / n_cu;
+    const int n_xcd_cu = std::max(1, std::min(n_cu / kXcds, 64));
+    const float idle = wide ? 0.70f : 0.88f;
+    // As locate_item deals them: whole heads to each XCD (then all eight do the same), or
+    // an eighth of all items.
+    const bool whole = Hkv % kXcds == 0;
+    const int all = items * Hkv, per = whole ? all / kXcds : (all + kXcds - 1) / kXcds;
+    float longest = 0.f;
+    for (int x = 0; x < (whole ? 1 : kXcds); ++x) {
+        float end[64] = {};                  // a heap: when each compute unit is free
+        float sum = 0.f, last = 0.f;
+        int at = (x * per) % items;
+        for (int w = x * per; w < std::min(all, (x + 1) * per); ++w) {
+            const float c = cost[at], t = end[0] + c;
+            at = at + 1 == items ? 0 : at + 1;
+            sum += c;
+            last = std::max(last, t);
+            int i = 0;
+            for (int c1; (c1 = 2 * i + 1) < n_xcd_cu; i = c1) {
+                if (c1 + 1 < n_xcd_cu && end[c1 + 1] < end[c1]) ++c1;
+                if (end[c1] >= t) break;
+                end[i] = end[c1];
+            }
+            end[i] = t;
+        }
+        longest = std::max(longest, idle * last + (1.f - idle) * sum / n_xcd_cu);
+    }
+    return longest;
 }
 
 // One launch over the sequences seq[0..n) (each with new tokens, n <= kMaxMapSeqs,
@@ -1348,47 +1383,11 @@ hipError_t launch_group(const int32_t *seq, int n, const u16 *qq, const pcr_kv_p
     auto rows_of = [&](int32_t b) { return ((int64_t)host_cu_suffix[b + 1] - host_cu_suffix[b]) * G; };
     const int sched = g_schedule.load(std::memory_order_relaxed);
     const bool prefer_keys = auto_schedule == PCR_ATTN_SCHEDULE_KEY_HALVES;
-    // More key-halves items than compute units: row halves when they are estimated to take
-    // less time (unless the caller prefers key halves, whose shorter workgroups free a
-    // compute unit sooner for copy kernels that share the device, and the row-halves items
-    // would not all fit the compute units at once). Row halves win where
-    // both fill whole rounds; they lose where their fewer items leave more of the last
-    // round idle, and where the suffixes are shorter than their tiles. Against taking them
-    // from two items per compute unit on (32 query / 8 kv heads of 128): 64 sequences of 32
-    // new tokens on 3000 cached 200 -> 154 us (key halves), 16 of 128 on 4096 142 -> 129 (row
-    // halves), one of 1280 on 8192 199 -> 180 and of 3584 on 8192 505 -> 473 (row halves);
-    // of 40 other shapes none lost 2%.
-    bool rows = sched == PCR_ATTN_SCHEDULE_ROW_HALVES;
-    if (sched == PCR_ATTN_SCHEDULE_AUTO) {
-        int64_t tiles = 0, tiles2 = 0;   // row tiles of 128 and of 256 rows, one kv head
-        for (int k = 0; k < n; ++k) {
-            tiles += (rows_of(seq[k]) + kRowsPerWG - 1) / kRowsPerWG;
-            tiles2 += (rows_of(seq[k]) + 2 * kRowsPerWG - 1) / (2 * kRowsPerWG);
-        }
-        auto time_of = [&](int rows_per_item) {
-            return schedule_time(seq, n, host_prefix_lens, host_cu_suffix, G, Hkv, pool.head_dim, rows_per_item, n_cu);
-        };
-        rows = tiles * Hkv > n_cu && (!prefer_keys || tiles2 * Hkv <= n_cu) &&
-               time_of(2 * kRowsPerWG) < time_of(kRowsPerWG);
-    }
-    const int64_t rpw = rows ? 2 * kRowsPerWG : kRowsPerWG;
-    // Key tiles per item, 0: no key split.
-    const int32_t chunk =
-        sched == PCR_ATTN_SCHEDULE_AUTO && !prefer_keys && !rows && can_split
-            ? split_chunk(seq, n, host_prefix_lens, host_cu_suffix, G, Hkv, n_cu)
-            : 0;
-    auto keys_of = [&](int32_t b) { return host_prefix_lens[b] + host_cu_suffix[b + 1] - host_cu_suffix[b]; };
-    auto tiles_of = [&](int32_t b) {
-        const int64_t t = (rows_of(b) + rpw - 1) / rpw;
-        return chunk ? t * ((key_tiles(keys_of(b) - 1) + chunk - 1) / chunk) : t;
-    };
-
     // Slot order: the given order (longest context first), with the decode rows (one
     // new token, one workgroup each, bound by HBM) spread evenly over the prefill
     // tiles (bound by the matrix cores): run back to back they would take every
     // compute unit at once and queue on HBM.
-    AttnWorkMap wm;
-    {
+    auto slot_order = [&](auto tiles_of, int32_t *order) {
         const bool dec_rows = G <= decode_wave::kMaxCols;
         int32_t pre[kMaxMapSeqs], dec[kMaxMapSeqs];
         int np = 0, nd = 0;
@@ -1404,12 +1403,58 @@ hipError_t launch_group(const int32_t *seq, int n, const u16 *qq, const pcr_kv_p
         int m = 0, di = 0;
         int64_t done = 0;
         for (int k = 0; k < np; ++k) {
-            wm.seq[m++] = pre[k];
+            order[m++] = pre[k];
             done += tiles_of(pre[k]);
-            for (; di < nd && (int64_t)di * pre_tiles < (int64_t)nd * done; ++di) wm.seq[m++] = dec[di];
+            for (; di < nd && (int64_t)di * pre_tiles < (int64_t)nd * done; ++di) order[m++] = dec[di];
         }
-        for (; di < nd; ++di) wm.seq[m++] = dec[di];
+        for (; di < nd; ++di) order[m++] = dec[di];
+    };
+
+    // More key-halves items than compute units: row halves from two of their items per
+    // compute unit on (each then pays its start and end for twice the work), and on either
+    // side of that line the other schedule when it is estimated to take 4% less. Key
+    // halves win where the fewer row-halves items leave more of the last round idle, and
+    // where the suffixes are shorter than their tiles. A caller that prefers key halves (whose
+    // shorter workgroups free a compute unit sooner for copy kernels that share the device)
+    // gets row halves only if they are estimated so and all fit the compute units at once.
+    // Against the line alone (32 query / 8 kv heads of 128): 64 sequences of 32 new tokens on
+    // 3000 cached 200 -> 154 us (key halves), 16 of 128 on 4096 142 -> 129 (row halves), one of
+    // 1280 on 8192 199 -> 180.
+    bool rows = sched == PCR_ATTN_SCHEDULE_ROW_HALVES;
+    if (sched == PCR_ATTN_SCHEDULE_AUTO) {
+        int64_t tiles = 0, tiles2 = 0;   // row tiles of 128 and of 256 rows, all kv heads
+        for (int k = 0; k < n; ++k) {
+            tiles += (rows_of(seq[k]) + kRowsPerWG - 1) / kRowsPerWG;
+            tiles2 += (rows_of(seq[k]) + 2 * kRowsPerWG - 1) / (2 * kRowsPerWG);
+        }
+        tiles *= Hkv;
+        tiles2 *= Hkv;
+        if (tiles > n_cu && (!prefer_keys || tiles2 <= n_cu)) {
+            const bool simulate = tiles <= std::min(4 * n_cu, kSimItems);
+            auto time_of = [&](int rpw) {
+                int32_t order[kMaxMapSeqs];
+                slot_order([&](int32_t b) { return (rows_of(b) + rpw - 1) / rpw; }, order);
+                return schedule_time(order, n, host_prefix_lens, host_cu_suffix, G, Hkv, pool.head_dim, rpw, n_cu,
+                                     simulate);
+            };
+            const bool line = tiles2 >= 2 * (int64_t)n_cu;
+            rows = time_of(2 * kRowsPerWG) < (line ? 1.04 : 0.96) * time_of(kRowsPerWG);
+        }
     }
+    const int64_t rpw = rows ? 2 * kRowsPerWG : kRowsPerWG;
+    // Key tiles per item, 0: no key split.
+    const int32_t chunk =
+        sched == PCR_ATTN_SCHEDULE_AUTO && !prefer_keys && !rows && can_split
+            ? split_chunk(seq, n, host_prefix_lens, host_cu_suffix, G, Hkv, n_cu)
+            : 0;
+    auto keys_of = [&](int32_t b) { return host_prefix_lens[b] + host_cu_suffix[b + 1] - host_cu_suffix[b]; };
+    auto tiles_of = [&](int32_t b) {
+        const int64_t t = (rows_of(b) + rpw - 1) / rpw;
+        return chunk ? t * ((key_tiles(keys_of(b) - 1) + chunk - 1) / chunk) : t;
+    };
+
+    AttnWorkMap wm;
+    slot_order(tiles_of, wm.seq);
     int32_t cum = 0;
     for (int k = 0; k < n; ++k) {
         const int32_t b = wm.seq[k];

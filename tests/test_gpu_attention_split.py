@@ -248,3 +248,39 @@ def test_default_schedule_of_one_to_four_rounds(pl, sl, G, Hkv, d):
         torch.cuda.synchronize()
         same.append(torch.equal(L.out, got))
     assert any(same)
+
+
+@pytest.mark.parametrize("pl,sl,G,Hkv,d,faster", [
+    # triangular items of 2 to 34 key tiles: 79 us with key halves, 103 with row halves
+    ([98, 74], [2117, 2082], 7, 4, 128, "key_halves"),
+    # 1.09 row-halves items per compute unit: 47 and 52 us
+    ([717] * 5, [315] * 5, 5, 8, 128, "key_halves"),
+    # 2.66, 64 dims: 717 and 655 us; 3.75: 468 and 423
+    ([12972] * 5, [541] * 5, 16, 4, 64, "row_halves"), ([4683] * 3, [2544] * 3, 4, 8, 64, "row_halves"),
+    # one row-halves item each for suffixes of half a tile: 154 and 200 us
+    ([3000] * 64, [32] * 64, 4, 8, 128, "key_halves"),
+])
+def test_default_schedule_is_the_faster_one(pl, sl, G, Hkv, d, faster):
+    """Where the two schedules differ in time the default takes the faster: its bits."""
+    say(f"[gpu] default schedule B={len(pl)} s={sl[0]} p={pl[0]} G={G} Hkv={Hkv} d={d}: {faster}")
+    need = [-(-(p + n) // BS) for p, n in zip(pl, sl)]
+    nb, T = sum(need), sum(sl)
+    bt = np.full((len(pl), max(need)), -1, np.int32)
+    off = 0
+    for b, n in enumerate(need):
+        bt[b, :n] = np.arange(off, off + n)
+        off += n
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(G + T)
+    k, v = (torch.randn(nb, Hkv, BS * d, device="cuda", generator=gen).bfloat16() for _ in range(2))
+    q = torch.randn(T, G * Hkv, d, device="cuda", generator=gen).bfloat16()
+    hp, hc = np.asarray(pl, np.int32), np.concatenate([[0], np.cumsum(sl)]).astype(np.int32)
+    bt, pl_d, cu_d = (torch.from_numpy(x).cuda() for x in (bt, hp, hc))
+    outs = {}
+    for name in ("auto", "key_halves", "row_halves"):
+        outs[name] = torch.zeros_like(q)
+        with attn_schedule(name):
+            pcr.prefix_prefill_attn(q, pcr.KVPool(k, v, Hkv, d), bt, pl_d, cu_d, hp, hc, G * Hkv, outs[name])
+        torch.cuda.synchronize()
+    assert not torch.equal(outs["key_halves"], outs["row_halves"])
+    assert torch.equal(outs["auto"], outs[faster])
