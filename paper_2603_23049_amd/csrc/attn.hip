@@ -388,12 +388,13 @@ __device__ __forceinline__ Item locate_item(const AttnWorkMap &wm, int32_t Hkv)
 // Output of one wave's 32 rows x W dims through LDS, so that whole lines leave it 16
 // bytes a lane. In the accumulator layout a lane holds 4 consecutive dims of its row at
 // a time: stored directly (8 bytes a lane, 32 rows in one instruction) the rows' lines
-// went out in 32-byte pieces, and a workgroup's end waited for them: 4.9 us from one
-// workgroup's last store to the next one's start on its compute unit, 1.3 us with
-// whole lines (256 rows x 128 dims; the turnover itself is 0.25 us).
+// went out in 32-byte pieces, and a workgroup's end waited for them: from the first wave's
+// last store to the next workgroup's start on the compute unit 4.0 us, 1.6 us with whole
+// lines (row halves, a ragged batch of 23 rounds; 3.9 and 1.1 us at the 70B layer).
 // Rows of W bf16 lie back to back in the wave's own LDS area; 16-byte chunk c of row q is
-// at chunk c ^ (q % (W/8)), and its two 8-byte halves change places in rows 16.., so that
-// neither the 8-byte writes nor the 16-byte reads meet in a bank.
+// at chunk c ^ (q % (W/8)), and its two 8-byte halves change places in rows 16.., so that the
+// 32 lanes of a half wave write every bank once and 16 lanes read every bank once. (The
+// conflict counter still shows 64 cycles a wave with row halves, 32 with key halves.)
 template <int W>
 __device__ __forceinline__ void stage_row(char *stage, int lane, int chunk, f32x4 v)
 {
