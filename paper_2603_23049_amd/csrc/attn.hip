@@ -1263,40 +1263,57 @@ void launch_attn(dim3 grid, hipStream_t s, const u16 *qq, const u16 *pk, const u
 // compute units idle while each workgroup walks every key; cutting the row tiles' keys
 // into chunks gives each compute unit one item. The chunk is the smallest one whose
 // items still fit the compute units (and the scratch) in one round.
-// A key tile takes a workgroup 0.58 us with few compute units busy and 0.75-0.9 us with
-// all of them (the clock follows the power); the claim, the partial results and the
-// combine kernel together cost about 9 us, i.e. 14 tiles. So the split is taken when
-// the longest item has at least 4/3 chunk + 14 tiles. Measured (32 query / 8 kv heads of
-// 128, unsplit -> split): 43 new tokens on 7985 cached 77 -> 23 us; 16 on 2000 25 -> 18;
-// 128 on 4000 44.5 -> 24; 400 on 4000 47 -> 41; 2 on 16000 143 -> 25; 1024 on 15360
-// twice with 8 / 1 heads 150 -> 124. Near the line: 16 on 1250 18.8 -> 17.3, 512 on 4000
-// 48.9 -> 46, 640 on 4000 53 -> 52 us; 16 on 1100 (17.8 us) stays whole. (Chunks of at
-// least 4, 6, 8, 12 or 16 tiles: 4 to 8 alike, 12 and 16 up to 20% slower on prefixes
-// of 2k.)
+// It is taken when it is estimated to take 6% less than the launch as a whole, per call
+// among others. In us, with f and g the shares of the compute units that have an item
+// whole and split, and L and c the key tiles of the longest row and of a chunk, row tiles of
+// 128 dims take 8.7 + (0.53 + 0.19 f) L whole and 18 + (0.40 + 0.46 g) c split, decode rows 5.5 + (0.59 +
+// 0.20 f) L and 16.5 + (0.26 + 0.65 g) c; with 64 dims 6.9 + (0.51 + 0.09 f) L and 16.5 + (0.44 +
+// 0.12 g) c, and 4.7 + (0.29 + 0.12 f) L and 15.5 + (0.31 + 0.06 g) c (fitted to 800 launches, within
+// 3% whole and 7% split; a full chip runs at a lower clock, and the three launches of a split
+// call are host-bound below 16 us). Measured (32 query / 8 kv heads of 128, whole ->
+// split): 43 new tokens on 7985 cached 77 -> 23 us; 16 on 2000 25 -> 18; 128 on 4000 44.5 ->
+// 24; 2 on 16000 143 -> 25; 1024 on 15360 twice with 8 / 1 heads 150 -> 124. On the 800, of 20 to
+// 140 tiles, one split launch is more than 1% slower than whole, by 2%; 14 tiles above 4/3
+// chunk as the line, whatever the rows and dims, had 73 slower ones, up to 57% (a decode
+// row of 64 dims on 1250 keys). (Chunks of at least 4, 6, 8, 12 or 16 tiles: 4 to 8 alike, 12
+// and 16 up to 20% slower on prefixes of 2k.)
 int32_t split_chunk(const int32_t *seq, int n, const int32_t *host_prefix_lens, const int32_t *host_cu_suffix, int G,
-                    int Hkv, int n_cu)
+                    int Hkv, int D, int n_cu)
 {
     const int64_t cap = std::min(n_cu, kSplitParts);
-    int32_t longest = 0;
-    for (int k = 0; k < n; ++k)
-        longest = std::max(longest, key_tiles(host_prefix_lens[seq[k]] + host_cu_suffix[seq[k] + 1] -
-                                              host_cu_suffix[seq[k]] - 1));
-    auto items = [&](int32_t c) {
+    int32_t longest[2] = {0, 0};             // key tiles: of the row tiles, of the decode rows
+    for (int k = 0; k < n; ++k) {
+        const int32_t b = seq[k], sb = host_cu_suffix[b + 1] - host_cu_suffix[b];
+        int32_t &l = longest[sb == 1 && G <= decode_wave::kMaxCols];
+        l = std::max(l, key_tiles(host_prefix_lens[b] + sb - 1));
+    }
+    auto items = [&](int32_t c) {            // of chunks of c tiles (0: whole)
         int64_t w = 0;
         for (int k = 0; k < n; ++k) {
             const int32_t b = seq[k], sb = host_cu_suffix[b + 1] - host_cu_suffix[b];
             w += ((int64_t)sb * G + kRowsPerWG - 1) / kRowsPerWG *
-                 ((key_tiles(host_prefix_lens[b] + sb - 1) + c - 1) / c);
+                 (c ? (key_tiles(host_prefix_lens[b] + sb - 1) + c - 1) / c : 1);
         }
         return w * Hkv;
     };
-    int32_t lo = kSplitMinChunk, hi = (longest - 14) * 3 / 4;
+    int32_t lo = kSplitMinChunk, hi = (std::max(longest[0], longest[1]) - 14) * 3 / 4;   // (never taken above)
     if (lo > hi || items(hi) > cap) return 0;
     while (lo < hi) {
         const int32_t mid = lo + (hi - lo) / 2;
         if (items(mid) <= cap) hi = mid; else lo = mid + 1;
     }
-    return hi;
+    static const float kTime[2][2][6] = {    // [64 dims, 128][row tile, decode row]
+        {{6.9f, 0.51f, 0.09f, 16.5f, 0.44f, 0.12f}, {4.7f, 0.29f, 0.12f, 15.5f, 0.31f, 0.06f}},
+        {{8.7f, 0.53f, 0.19f, 18.f, 0.40f, 0.46f}, {5.5f, 0.59f, 0.20f, 16.5f, 0.26f, 0.65f}}};
+    const float f = (float)items(0) / n_cu, g = (float)items(hi) / n_cu;
+    float whole = 0.f, split = 0.f;
+    for (int kind = 0; kind < 2; ++kind) {
+        if (!longest[kind]) continue;
+        const float *t = kTime[D == 128][kind];
+        whole = std::max(whole, t[0] + (t[1] + t[2] * f) * longest[kind]);
+        split = std::max(split, t[3] + (t[4] + t[5] * g) * std::min(hi, longest[kind]));
+    }
+    return split < 0.94f * whole ? hi : 0;
 }
 
 // Estimated time in us of a launch on row tiles of rpw rows (128: key halves, 256: row
@@ -1446,7 +1463,7 @@ hipError_t launch_group(const int32_t *seq, int n, const u16 *qq, const pcr_kv_p
     // Key tiles per item, 0: no key split.
     const int32_t chunk =
         sched == PCR_ATTN_SCHEDULE_AUTO && !prefer_keys && !rows && can_split
-            ? split_chunk(seq, n, host_prefix_lens, host_cu_suffix, G, Hkv, n_cu)
+            ? split_chunk(seq, n, host_prefix_lens, host_cu_suffix, G, Hkv, pool.head_dim, n_cu)
             : 0;
     auto keys_of = [&](int32_t b) { return host_prefix_lens[b] + host_cu_suffix[b + 1] - host_cu_suffix[b]; };
     auto tiles_of = [&](int32_t b) {
