@@ -18,13 +18,14 @@ typedef unsigned short u16;
 // Output rows per gather workgroup: 16 and 64 were 2-5% slower on 268 MB, 16 20% on two
 // kv heads.
 constexpr int kGatherTile = 32;
-// Bytes of input (append) or output (gather) from which both go past the caches: non-
+// Bytes of input (append) or output (gather) above which both go past the caches: non-
 // temporal loads and, for gather, stores. Appends of 16k, 20k and 32k tokens of 8 kv heads
 // of 128 (4 KB a token), ordinary -> non-temporal loads: 40 -> 31, 49 -> 39 and 72 -> 61 us
 // when the input has left the caches; 25 -> 28, 31 -> 35 and 49 -> 54 in ragged sequences,
 // 22 -> 22, 27 -> 27 and 45 -> 49 in aligned ones, when the layer's passes have just written
-// it (28, 34, 54 and 22, 27, 44 with tiles cut at token 32). Smaller inputs are cached more
-// often, and lose 12-20% (14-33 MB).
+// it (28, 34, 54 and 22, 27, 44 with tiles cut at token 32). 16k tokens, the line itself, whose
+// input and output fill half of the 256 MB cache, lose 3 us when they are appended again
+// and again (22 -> 25 aligned, 25 -> 28 ragged), and smaller inputs 12-20% (14-33 MB).
 constexpr int64_t kNtBytes = 64ll << 20;
 // Output bytes up to which gather runs one thread per 16 bytes of a row (gather_rows_kernel).
 constexpr int64_t kGatherRowsBytes = 4ll << 20;
@@ -209,7 +210,7 @@ __global__ __launch_bounds__(256) void append_kv_kernel(
 // kernel that reads its output together, with input out of the caches, took 42 us for 8192
 // tokens of 8 kv heads of 128 by 2-byte loads, 43 with non-temporal stores, 38 without;
 // 16384 (67 MB out) 82, 73, 68, 65536 308, 224, 222; with cached input 16384 65, 48, 48, 32768
-// 151, 93, 103. So they start at kNtBytes.
+// 151, 93, 103. So they start above kNtBytes.
 // A row whose block is not in the pool or past the table is written as zeros.
 // ---------------------------------------------------------------------------
 template <int D, int TILE, bool NT>
@@ -422,7 +423,7 @@ hipError_t launch_append_kv(const pcr_kv_pool &pool, const void *k_new, const vo
     const int64_t in_bytes = 2 * (int64_t)T * pool.num_kv_heads * pool.head_dim * 2;
     auto launch_d = [&](auto dim) {
         constexpr int D = decltype(dim)::value;
-        if (in_bytes >= kNtBytes) launch(append_kv_kernel<D, kAppendTile, true, false>);
+        if (in_bytes > kNtBytes) launch(append_kv_kernel<D, kAppendTile, true, false>);
         else if ((int64_t)grid.x * grid.y <= kAppendEarly) launch(append_kv_kernel<D, kAppendTile, false, true>);
         else launch(append_kv_kernel<D, kAppendTile, false, false>);
     };
@@ -446,7 +447,7 @@ hipError_t launch_gather_kv(const pcr_kv_pool &pool, const int32_t *block_tables
     auto launch_d = [&](auto dim) {
         constexpr int DD = decltype(dim)::value;
         if (out_bytes <= kGatherRowsBytes) launch(gather_rows_kernel<DD>, 256 / (DD / 8));
-        else if (out_bytes >= kNtBytes) launch(gather_kv_kernel<DD, kGatherTile, true>, kGatherTile);
+        else if (out_bytes > kNtBytes) launch(gather_kv_kernel<DD, kGatherTile, true>, kGatherTile);
         else launch(gather_kv_kernel<DD, kGatherTile, false>, kGatherTile);
     };
     if (D == 128) launch_d(std::integral_constant<int, 128>{});

@@ -122,8 +122,10 @@ def test_split_launches_on_many_streams():
     assert pcr.prefill_attn_hold_scratch(0) == 64
 
 
-@pytest.mark.parametrize("pl,sl,G,Hkv,d", [([3000], [20], 4, 8, 128), ([2500], [70], 5, 3, 64), ([4000], [1], 4, 8, 128),
-                                           ([3000, 2000, 10], [1, 33, 1], 8, 2, 64)])
+@pytest.mark.parametrize("pl,sl,G,Hkv,d", [
+    ([3000], [20], 4, 8, 128), ([2500], [70], 5, 3, 64), ([4000], [1], 4, 8, 128),
+    ([3000, 2000, 10], [1, 33, 1], 8, 2, 64),
+])
 def test_launch_that_finds_the_scratch_taken_runs_whole(pl, sl, G, Hkv, d):
     """With every part of the scratch held, a call and a replay of a captured call take every
     key in one piece (the bits of key halves, tile rows and one-token rows); with one part
