@@ -59,7 +59,11 @@ CASES = [
 ]
 
 
-@pytest.mark.parametrize("pl,sl,G,Hkv,d", CASES)
+# Few workgroups, but keys too short to gain by it: 14 us whole, 17 us cut.
+WHOLE = [([2047], [1], 16, 2, 64)]
+
+
+@pytest.mark.parametrize("pl,sl,G,Hkv,d", CASES + WHOLE)
 def test_split_launch_against_oracle(pl, sl, G, Hkv, d):
     say(f"[gpu] key split p={pl} s={sl} G={G} Hkv={Hkv} d={d}")
     L, rows, want = _layer(pl, sl, G, Hkv, d, seed=300 + len(pl) + G + sl[0])
@@ -74,7 +78,7 @@ def test_split_launch_against_oracle(pl, sl, G, Hkv, d):
     with attn_schedule("key_halves"):
         L.attn()
     torch.cuda.synchronize()
-    assert not torch.equal(L.out, first), "the default schedule did not split these keys"
+    assert torch.equal(L.out, first) == ((pl, sl, G, Hkv, d) in WHOLE), "the default schedule's choice for these keys"
 
 
 def test_split_launch_replayed_from_a_graph_beside_eager_calls():
